@@ -160,12 +160,12 @@ typedef struct {
                                  multiplier), w = xbar (1) or vbar (2), xbar.  Trace rows
                                  hold [y, v, x, ybar, vbar, xbar] (method 1: x in the v
                                  places).  Per-solve option; 0                               */
-  int32_t kron_kernel;        /* HPRQP_Q_KRON product kernel: -1 choose (the K-split kernel for
-                                 factors up to 384, else the LDS-tiled one, timed against each
-                                 other when spmv_autotune = 1); 0: K-split kernel (one 16 x 16
-                                 tile per block, K over 8 waves); 1, 2, 4, 8: LDS-tiled kernel
-                                 (64 x 64 tiles) with that many split-K groups (2 to 8 only
-                                 while the tiles are fewer than 4 per compute unit); -1      */
+  int32_t kron_kernel;        /* HPRQP_Q_KRON product: -1 choose (tiles of the output by its
+                                 size, split-K groups only where large factors leave half of
+                                 the compute units without a tile; the choices are timed against
+                                 each other when spmv_autotune = 1); 0: 16 x 16 tiles; 1, 2, 4,
+                                 8: tiles by size with that many split-K groups (2 to 8 only
+                                 while 64 x 64 tiles would be fewer than 4 per compute unit); -1 */
   int32_t small_path;         /* method 0 with explicit (CSR) or zero Q: run each check segment
                                  as one workgroup (the four products as phases separated by
                                  barriers, same fused epilogues) instead of four launches per

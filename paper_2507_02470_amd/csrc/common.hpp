@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #define HQ_WAVE 64
 #define HQ_BLOCK 256          // threads per block for vector/SpMV kernels (4 waves)
@@ -151,6 +152,25 @@ __device__ __forceinline__ double ld_stream(const double* p) { return __builtin_
 __device__ __forceinline__ int ld_stream(const int* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ unsigned short ld_stream(const unsigned short* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void st_stream(double* p, double v) { __builtin_nontemporal_store(v, p); }
+
+// Operands of row i of an epilogue that lists them (a type with Ops, load(i) and
+// operator()(i, q, acc, ops)): a product issues these loads before its own, so
+// that they arrive during it.  Every epilogue reads and writes its own row only,
+// and no vector that a product gathers is written by that product.
+template <class E, class = void>
+struct EpiOps {
+  struct type {};
+  static __device__ __forceinline__ type load(const E&, int) { return {}; }
+  static __device__ __forceinline__ void run(const E& e, int i, double q, double* acc, const type&) { e(i, q, acc); }
+};
+template <class E>
+struct EpiOps<E, std::void_t<typename E::Ops>> {
+  using type = typename E::Ops;
+  static __device__ __forceinline__ type load(const E& e, int i) { return e.load(i); }
+  static __device__ __forceinline__ void run(const E& e, int i, double q, double* acc, const type& o) {
+    e(i, q, acc, o);
+  }
+};
 
 static inline int hq_grid(long long work, int per_block) {
   long long g = (work + per_block - 1) / per_block;

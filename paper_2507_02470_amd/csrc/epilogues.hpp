@@ -30,10 +30,13 @@ struct EpiQ1 {
   static constexpr bool PANEL_PREFETCH = true;
   static constexpr unsigned MAXMASK = 0u;
   __device__ void setup(const DevParams* p, int j) { IterScalars s; s.load(p, j); kappa = s.kappa; }
-  __device__ __forceinline__ void operator()(int i, double q, double*) const {
+  struct Ops { double xh, Qw; };
+  __device__ __forceinline__ Ops load(int i) const { return Ops{xh[i], ld_stream(Qw + i)}; }
+  __device__ __forceinline__ void operator()(int i, double q, double*, const Ops& o) const {
     st_stream(q1 + i, q);                                   // read once, by Q-apply #2
-    v[i] = xh[i] + kappa * (ld_stream(Qw + i) - q);          // v is gathered next: keep it cached
+    v[i] = o.xh + kappa * (o.Qw - q);                       // v is gathered next: keep it cached
   }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
 };
 
 // A-product:  r_y = A v - sigma lamA y;  ybar = (Pi_K(r_y) - r_y)/(sigma lamA)  ("update-y");
@@ -47,10 +50,15 @@ struct EpiY {
   static constexpr int NR = 2;
   static constexpr unsigned MAXMASK = 0u;
   __device__ void setup(const DevParams* p, int j) { IterScalars s; s.load(p, j); sA = s.sA; rho = s.rho; }
-  __device__ __forceinline__ void operator()(int i, double q, double* acc) const {
-    const double yi = ld_stream(y + i), yai = ld_stream(ya + i);
+  struct Ops { double y, ya, l, u; };
+  __device__ __forceinline__ Ops load(int i) const {
+    return Ops{ld_stream(y + i), ld_stream(ya + i), ld_stream(l + i), ld_stream(u + i)};
+  }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc, const Ops& o) const {
+    const double yi = o.y, yai = o.ya;
     const double r = q - sA * yi;
-    const double yb = (clampd(r, ld_stream(l + i), ld_stream(u + i)) - r) / sA;
+    const double yb = (clampd(r, o.l, o.u) - r) / sA;
     ybar[i] = yb;                                            // gathered next by A^T
     st_stream(y + i, rho * yai + (1.0 - rho) * (2.0 * yb - yi));
     if (want_r) { const double t = yi - yb; acc[0] += t * t; }
@@ -68,8 +76,11 @@ struct EpiAT {
   static constexpr int NR = 0;
   static constexpr unsigned MAXMASK = 0u;
   __device__ void setup(const DevParams* p, int j) { IterScalars s; s.load(p, j); rho = s.rho; }
-  __device__ __forceinline__ void operator()(int i, double q, double*) const {
-    const double aty = ld_stream(ATy + i), atya = ld_stream(ATya + i);
+  struct Ops { double aty, atya; };
+  __device__ __forceinline__ Ops load(int i) const { return Ops{ld_stream(ATy + i), ld_stream(ATya + i)}; }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
+  __device__ __forceinline__ void operator()(int i, double q, double*, const Ops& o) const {
+    const double aty = o.aty, atya = o.atya;
     d[i] = q - aty;                                          // gathered next by Q-apply #2
     st_stream(ATy + i, rho * atya + (1.0 - rho) * (2.0 * q - aty));
     if (check) { g[i] = q; e[i] = q - atya; }
@@ -112,23 +123,21 @@ struct EpiQ2 {
   __device__ __forceinline__ Pre preload(int i) const {
     return Pre{ld_stream(wa + i), ld_stream(Qwa + i), ld_stream(xa + i)};
   }
+  struct Ops { double xh, w, Qw, d, q1, wa, Qwa, xa, ATy, c, L, U; };
+  __device__ __forceinline__ Ops load(int i, const Pre& p) const {
+    return Ops{ld_stream(xh + i), ld_stream(w + i), ld_stream(Qw + i), d[i], ld_stream(q1 + i), p.wa, p.Qwa, p.xa,
+               ld_stream(ATy + i), ld_stream(c + i), ld_stream(L + i), ld_stream(U + i)};
+  }
+  __device__ __forceinline__ Ops load(int i) const { return load(i, preload(i)); }
   __device__ __forceinline__ void operator()(int i, double q2, double* acc, const Pre& pf) const {
-    apply(i, q2, acc, [&](double& a, double& b, double& c3) { a = pf.wa; b = pf.Qwa; c3 = pf.xa; });
+    (*this)(i, q2, acc, load(i, pf));
   }
-  __device__ __forceinline__ void operator()(int i, double q2, double* acc) const {
-    apply(i, q2, acc, [&](double& a, double& b, double& c3) {
-      a = ld_stream(wa + i); b = ld_stream(Qwa + i); c3 = ld_stream(xa + i);
-    });
-  }
-  // anchors(wa_i, Qwa_i, xa_i) supplies the Halpern anchors of entry i
-  template <class Anchors>
-  __device__ __forceinline__ void apply(int i, double q2, double* acc, Anchors anchors) const {
-    const double xhi = ld_stream(xh + i), wi = ld_stream(w + i), Qwi = ld_stream(Qw + i), di = d[i];
+  __device__ __forceinline__ void operator()(int i, double q2, double* acc) const { (*this)(i, q2, acc, load(i)); }
+  __device__ __forceinline__ void operator()(int i, double q2, double* acc, const Ops& o) const {
+    const double xhi = o.xh, wi = o.w, Qwi = o.Qw, di = o.d, wai = o.wa, Qwai = o.Qwa, xai = o.xa;
     const double inv = 1.0 / (1.0 + sQ);
     const double wb = (sQ * wi + xhi) * inv + kappa * di;
-    const double Qwb = (sQ * Qwi + ld_stream(q1 + i)) * inv + kappa * q2;
-    double wai, Qwai, xai;
-    anchors(wai, Qwai, xai);
+    const double Qwb = (sQ * Qwi + o.q1) * inv + kappa * q2;
     if (want_r || check || trace) {
       const double xb = XB[i];
       if (want_r) {
@@ -148,8 +157,8 @@ struct EpiQ2 {
     const double Qwn = rho * Qwai + (1.0 - rho) * (2.0 * Qwb - Qwi);
     st_stream(w + i, wn); st_stream(Qw + i, Qwn);
     if (trace) x[i] = xn;
-    const double rz = xn + sigma * (-Qwn + ld_stream(ATy + i) - ld_stream(c + i));
-    const double xbn = prox_phi(rz, sigma * l1, ld_stream(L + i), ld_stream(U + i));
+    const double rz = xn + sigma * (-Qwn + o.ATy - o.c);
+    const double xbn = prox_phi(rz, sigma * l1, o.L, o.U);
     xh[i] = 2.0 * xbn - xn;                                  // gathered next by Q-apply #1
     if (xb_next) { XB[i] = xbn; ZB[i] = (xbn - rz) / sigma; }
   }

@@ -255,8 +255,8 @@ struct hprqp_handle {
   const double *kS = nullptr, *kT = nullptr;   // QAP relaxation: Q = B (x) C - I (x) S - T (x) I
   int small_G = 0;            // > 0: segments run as one workgroup (k_small_segment<small_G>)
   bool small_forced = false;  // small_path = 1: also when the data does not fit the LDS
-  int kron_mode = 0;          // 0: k_dgemm16 (K split over waves), 1: LDS-tiled k_dgemm_tile
-  int kron_groups = 1;        // split-K groups of the tiled kernel
+  int kron_mode = 0;          // tiles of k_dgemm: 0: 16 x 16, 1: by gemm_tile_of
+  int kron_groups = 1;        // its split-K groups
   int kron_groups_max = 1;    // capacity of kparts (in n-vectors)
   double* kparts = nullptr;
   int lr_r = 0;
@@ -506,45 +506,80 @@ void final_reduce(hprqp_handle& h, int slot0, int nslot) {
   k_final_reduce<<<nslot, 256, 0, h.st>>>(h.partials, h.counts, slot0, kMaxMask, h.scalars);
 }
 
-// one term list through the tiled GEMM, split-K when h.kron_groups > 1
-template <class Epi>
-void launch_tile(hprqp_handle& h, int M, int N, const GemmOps& ops, const Epi& epi, int j, const RedOut& red) {
-  const int tiles = ((M + HQ_TB - 1) / HQ_TB) * ((N + HQ_TB - 1) / HQ_TB);
+inline int tile_count(int M, int N, int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); }
+
+// Tile of the GEMM, 16 WM x 16 WN as 10 WM + WN: the one that makes the busiest CU's
+// share of tiles cheapest.  A larger tile loads less per product (the weights
+// below, per 16 x 16 part).  Us per Q product of the QAP relaxation with 16 x 16,
+// 32 x 16, 32 x 32 and 64 x 32 tiles: d = 300 25, 20.3, 28.0, 38.8; d = 512 71, 46.4, 39.6,
+// 52.9; d = 700 159, 98, 79, 68; d = 1024 460, 285, 227, 170 (64 x 64: 176).
+// kron_kernel = 0 takes the smallest.
+int gemm_tile_of(const hprqp_handle& h, int M, int N) {
+  if (h.kron_mode == 0) return 11;
+  const int wm[] = {1, 2, 2, 4}, wn[] = {1, 1, 2, 2};
+  const double weight[] = {1.8, 1.25, 1.0, 0.8};
+  int best = 0;
+  double cost = 1e300;
+  for (int k = 0; k < 4; ++k) {
+    const long long tiles = tile_count(M, N, 16 * wm[k], 16 * wn[k]);
+    const double c = (double)((tiles + h.ncu - 1) / h.ncu * wm[k] * wn[k]) * weight[k];
+    if (c < cost) { cost = c; best = 10 * wm[k] + wn[k]; }
+  }
+  return best;
+}
+
+template <int WM, int WN, int NW, bool SHORT = false, class Epi>
+void launch_gemm_tile(hprqp_handle& h, int M, int N, const GemmOps& ops, const Epi& epi, int j, const RedOut& red) {
+  const int tiles = tile_count(M, N, 16 * WM, 16 * WN);
   const int G = h.kron_groups;
   if (G <= 1) {
     check_red_grid(std::min(tiles, HQ_GRID_CAP), red);
-    k_dgemm_tile<Epi, false><<<std::min(tiles, HQ_GRID_CAP), 256, 0, h.st>>>(M, N, ops, M, epi, h.dprm, j, red, 1,
-                                                                          nullptr);
+    k_dgemm<Epi, false, WM, WN, NW, SHORT><<<std::min(tiles, HQ_GRID_CAP), 64 * NW, 0, h.st>>>(
+        M, N, ops, M, epi, h.dprm, j, red, 1, nullptr);
   } else {
-    k_dgemm_tile<Epi, true><<<std::min(tiles * G, HQ_GRID_CAP), 256, 0, h.st>>>(M, N, ops, M, epi, h.dprm, j,
-                                                                             no_red(h), G, h.kparts);
+    k_dgemm<EpiStore, true, WM, WN, NW, SHORT><<<std::min(tiles * G, HQ_GRID_CAP), 64 * NW, 0, h.st>>>(
+        M, N, ops, M, EpiStore{nullptr}, h.dprm, j, no_red(h), G, h.kparts);
     const long long cnt = (long long)M * N;
     check_red_grid(hq_grid(cnt, HQ_BLOCK), red);
     k_gemm_sum<Epi><<<hq_grid(cnt, HQ_BLOCK), HQ_BLOCK, 0, h.st>>>(cnt, G, h.kparts, epi, h.dprm, j, red);
   }
 }
 
-// Kronecker / QAP-relaxation Q through the tiled GEMM: T1 = C X, then
+// one term list through the GEMM, split-K when h.kron_groups > 1
+template <class Epi>
+void launch_gemm(hprqp_handle& h, int M, int N, const GemmOps& ops, const Epi& epi, int j, const RedOut& red) {
+  bool is_short = false;
+  for (int t = 0; t < ops.nt; ++t) is_short |= ops.K[t] < 16;
+  if (is_short) { launch_gemm_tile<1, 1, 8, true>(h, M, N, ops, epi, j, red); return; }
+  switch (gemm_tile_of(h, M, N)) {
+    case 11: launch_gemm_tile<1, 1, 8>(h, M, N, ops, epi, j, red); break;
+    case 21: launch_gemm_tile<2, 1, 4>(h, M, N, ops, epi, j, red); break;
+    case 22: launch_gemm_tile<2, 2, 4>(h, M, N, ops, epi, j, red); break;
+    default: launch_gemm_tile<4, 2, 8>(h, M, N, ops, epi, j, red); break;
+  }
+}
+
+// Kronecker / QAP-relaxation Q: T1 = C X, then
 // Y = T1 B^T (- X T^T - S X) with the epilogue
 template <class Epi>
-void kron_tiled(hprqp_handle& h, const double* x, const Epi& epi, int j, const RedOut& red) {
+void kron_apply(hprqp_handle& h, const double* x, const Epi& epi, int j, const RedOut& red) {
   const int s = h.ks, p = h.kp;
   GemmOps g1{};
   g1.nt = 1;
-  g1.A[0] = h.kC; g1.lda[0] = s; g1.B[0] = x; g1.ldb[0] = s; g1.K[0] = s; g1.transb[0] = 0; g1.sign[0] = 1.0;
-  launch_tile(h, s, p, g1, EpiStore{h.kronT}, j, no_red(h));
+  g1.A[0] = h.kC; g1.lda[0] = s; g1.B[0] = x; g1.ldb[0] = s; g1.K[0] = s; g1.transb[0] = 0;
+  launch_gemm(h, s, p, g1, EpiStore{h.kronT}, j, no_red(h));
   GemmOps g2{};
   g2.nt = 1;
-  g2.A[0] = h.kronT; g2.lda[0] = s; g2.B[0] = h.kB; g2.ldb[0] = p; g2.K[0] = p; g2.transb[0] = 1; g2.sign[0] = 1.0;
+  g2.A[0] = h.kronT; g2.lda[0] = s; g2.B[0] = h.kB; g2.ldb[0] = p; g2.K[0] = p; g2.transb[0] = 1;
   if (h.kT) {
     const int t = g2.nt++;
-    g2.A[t] = x; g2.lda[t] = s; g2.B[t] = h.kT; g2.ldb[t] = p; g2.K[t] = p; g2.transb[t] = 1; g2.sign[t] = -1.0;
+    g2.A[t] = x; g2.lda[t] = s; g2.B[t] = h.kT; g2.ldb[t] = p; g2.K[t] = p; g2.transb[t] = 1; g2.neg[t] = 1;
   }
   if (h.kS) {
     const int t = g2.nt++;
-    g2.A[t] = h.kS; g2.lda[t] = s; g2.B[t] = x; g2.ldb[t] = s; g2.K[t] = s; g2.transb[t] = 0; g2.sign[t] = -1.0;
+    g2.A[t] = h.kS; g2.lda[t] = s; g2.B[t] = x; g2.ldb[t] = s; g2.K[t] = s; g2.transb[t] = 0; g2.neg[t] = 1;
   }
-  launch_tile(h, s, p, g2, epi, j, red);
+  launch_gemm(h, s, p, g2, epi, j, red);
 }
 
 // out-of-place Q product with a fused epilogue: epi(i, (Q x)_i).  heavy: the
@@ -565,36 +600,9 @@ void q_apply(hprqp_handle& h, const double* x, const Epi& epi, int j, const RedO
         launch_csr(h, h.Q, x, epi, j, red);
       }
       break;
-    case HPRQP_Q_KRON: {
-      // Q vec(X) = vec(C X B^T): T = C X, then Y = T B^T with the epilogue
-      const int s = h.ks, p = h.kp;
-      if (h.kron_mode == 1) {
-        kron_tiled(h, x, epi, j, red);
-        break;
-      }
-      const int tiles = ((s + 15) / 16) * ((p + 15) / 16);
-      const int grid = std::min(tiles, HQ_GRID_CAP);
-      check_red_grid(grid, red);
-      k_dgemm16<false, EpiStore><<<grid, 64 * HQ_KSPLIT, 0, h.st>>>(s, p, s, h.kC, s, x, s, s, EpiStore{h.kronT},
-                                                                    h.dprm, j, no_red(h));
-      if (!h.kS && !h.kT) {
-        k_dgemm16<true, Epi><<<grid, 64 * HQ_KSPLIT, 0, h.st>>>(s, p, p, h.kronT, s, h.kB, p, s, epi, h.dprm, j, red);
-      } else {
-        // QAP relaxation: Y = T1 B^T - X T^T - S X in one accumulation
-        GemmTerms ex{};
-        if (h.kT) {
-          const int t = ex.nt++;
-          ex.A[t] = x; ex.lda[t] = s; ex.B[t] = h.kT; ex.ldb[t] = p; ex.K[t] = p; ex.transb[t] = 1; ex.sign[t] = -1.0;
-        }
-        if (h.kS) {
-          const int t = ex.nt++;
-          ex.A[t] = h.kS; ex.lda[t] = s; ex.B[t] = x; ex.ldb[t] = s; ex.K[t] = s; ex.transb[t] = 0; ex.sign[t] = -1.0;
-        }
-        k_dgemm16<true, Epi, true><<<grid, 64 * HQ_KSPLIT, 0, h.st>>>(s, p, p, h.kronT, s, h.kB, p, s, epi, h.dprm,
-                                                                      j, red, ex);
-      }
+    case HPRQP_Q_KRON:
+      kron_apply(h, x, epi, j, red);
       break;
-    }
     case HPRQP_Q_GRAM:
       // Q x = Ahat^T (Ahat x): a plain product into gtmp, then the epilogue product
       launch_csr(h, h.G, x, EpiStore{h.gtmp}, j, no_red(h));
@@ -1052,18 +1060,15 @@ void autotune_csr(hprqp_handle& h, Mat& M, const double* x, double* out) {
   hipEventDestroy(e1);
 }
 
-// Kronecker Q: the K-split kernel for small factors (latency-bound, d ~ 300),
-// the LDS-tiled kernel above that, with split-K groups until there are 4
-// blocks per compute unit (one 4-wave block per CU leaves the MFMA pipes
-// waiting on LDS and L2; measured: d = 1024, 236 us with 4 groups against
-// 484 us with 1)
+// Kronecker Q: tiles by gemm_tile_of; split-K groups only for large factors
+// whose tiles leave half of the compute units idle (a non-square X)
 void default_kron(hprqp_handle& h) {
-  const int tiles = ((h.ks + HQ_TB - 1) / HQ_TB) * ((h.kp + HQ_TB - 1) / HQ_TB);
-  if (std::max(h.ks, h.kp) <= 384) { h.kron_mode = 0; h.kron_groups = 1; return; }
   h.kron_mode = 1;
-  int G = 1;
-  while (G < h.kron_groups_max && tiles * G < 4 * h.ncu) G *= 2;
-  h.kron_groups = G;
+  h.kron_groups = 1;
+  if (std::max(h.ks, h.kp) <= 384) return;
+  const int t = gemm_tile_of(h, h.ks, h.kp);
+  const int tiles = tile_count(h.ks, h.kp, 16 * (t / 10), 16 * (t % 10));
+  while (h.kron_groups < h.kron_groups_max && 2 * tiles * h.kron_groups <= h.ncu) h.kron_groups *= 2;
 }
 
 // time the Kronecker variants on a full Q product; keep the default unless
@@ -1220,7 +1225,7 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
     if (h.qkind == HPRQP_Q_KRON) {
       h.kronT = h.dalloc<double>(n);
       // split-K workspace of the tiled GEMM while its tiles are fewer than 4 per CU
-      const int tiles = ((h.ks + HQ_TB - 1) / HQ_TB) * ((h.kp + HQ_TB - 1) / HQ_TB);
+      const int tiles = tile_count(h.ks, h.kp, 64, 64);
       h.kron_groups_max = tiles < 4 * h.ncu ? 8 : 1;
       if (h.kron_groups_max > 1) h.kparts = h.dalloc<double>((size_t)h.kron_groups_max * n);
       default_kron(h);
@@ -2148,7 +2153,7 @@ void residuals_noalloc_impl(const hprqp_problem* P, const double* y, const doubl
   if (P->qkind == HPRQP_Q_CSR) h.Q = Mat{n, n, P->q_rowptr, P->q_col, P->q_val, P->q_nnz, default_G(P->q_nnz, n, hf[2], n)};
   if (P->qkind == HPRQP_Q_KRON) {
     h.kp = P->kron_p; h.ks = P->kron_s; h.kB = P->kron_B; h.kC = P->kron_C; h.kS = P->kron_S; h.kT = P->kron_T;
-    h.kron_mode = 0;
+    h.kron_mode = 1;
   }
   if (P->qkind == HPRQP_Q_LOWRANK) { h.lr_r = P->lr_rank; h.lr_d = P->lr_d; h.lr_F = P->lr_F; }
   if (P->qkind == HPRQP_Q_GRAM)

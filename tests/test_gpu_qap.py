@@ -68,6 +68,30 @@ def test_qap_operator_matches_oracle(d, terms, kernel):
     s.close()
 
 
+@pytest.mark.parametrize("s,p,kernel", [(1, 1, -1), (3, 40, -1), (15, 17, -1), (16, 33, -1), (31, 32, 2), (300, 290, -1),
+                                        (401, 397, -1), (512, 30, -1), (513, 511, -1), (690, 705, -1), (705, 690, 2)])
+def test_kron_tiles(s, p, kernel):
+    """Non-square X and unsymmetric factors at the sizes where the tile changes
+    (16 x 16, 32 x 16, 32 x 32, 64 x 32), where K is below, at and past a block of 16, and
+    with split-K groups.  Bound: a dot product of K terms is off by at most K u times
+    the sum of its absolute terms in any order; here K = s, then p + p + s."""
+    DP, Solver = _S()
+    rng = np.random.default_rng(1000 * s + p)
+    C, S = rng.standard_normal((2, s, s))
+    B, T = rng.standard_normal((2, p, p))
+    qp = qpgen.QP(n=s * p, m=0, qkind="kron", c=np.zeros(s * p), L=np.full(s * p, -1.0), U=np.ones(s * p),
+                  a_rowptr=np.zeros(1, dtype=np.int32), a_col=np.zeros(0, dtype=np.int32), a_val=np.zeros(0),
+                  l=np.zeros(0), u=np.zeros(0), kron_B=B, kron_C=C, kron_S=S, kron_T=T)
+    print(f"kron tiles s={s} p={p} kernel={kernel}", flush=True)
+    h = Solver(DP(qp), lambda_A=1.0, lambda_Q=1.0, tol=0.0, max_iter=1, kron_kernel=kernel)
+    X = rng.standard_normal((s, p))
+    got = h.apply("Q", X.ravel(order="F")).cpu().numpy().reshape((s, p), order="F")
+    want = C @ X @ B.T - X @ T.T - S @ X
+    size = np.abs(C) @ np.abs(X) @ np.abs(B.T) + np.abs(X) @ np.abs(T.T) + np.abs(S) @ np.abs(X)
+    assert np.all(np.abs(got - want) <= 2 * (2 * s + 2 * p + 16) * 2.0 ** -53 * size)   # both sides round
+    h.close()
+
+
 @pytest.mark.parametrize("d,check_every,kernel", [(9, 7, -1), (16, 10, -1), (16, 10, 1), (67, 10, 4)])
 def test_qap_iterates_match_oracle(d, check_every, kernel):
     DP, Solver = _S()
