@@ -7,12 +7,21 @@
 // dimension padded to a multiple of 8 and zero-filled), which lets each
 // lane fetch its 8 consecutive K values of a v_mfma_f32_32x32x16_bf16
 // operand with one 16-byte load.
+//
+// A training step's arithmetic is a few microseconds on this chip; what it costs
+// is launches and the latency chain of each.  So every elementwise step
+// (standardization, bias, GELU, loss gradient, GELU', the BF16 copies and their
+// transposes) runs in the epilogue of the GEMM that produces its operand, the K
+// splits of a GEMM are waves of one block, and GEMMs that do not depend on each
+// other share a launch: 7 launches for loss_grad and 1 for Adam (35 before;
+// batch 256, 1021-512-512-2022, the whole step: 270 -> 98 us).
 #include "hprqp_mlp.h"
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace hq {
@@ -36,26 +45,8 @@ __device__ __forceinline__ float gelu_d(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
 }
 
-// Optional epilogue of a GEMM of the forward pass: Z = A B + bias (FP32,
-// stored in C) and, with act, its activation as BF16 (GELU for the hidden
-// layers): the same FP32 operations as a separate bias/activation pass.
-struct GemmEpi {
-  const float* bias = nullptr;
-  uint16_t* act = nullptr;
-  long long ld_act = 0;
-  int gelu_on = 0;
-};
-__device__ __forceinline__ void gemm_store(float* C, long long ldc, int row, int col, float v, int accumulate,
-                                           const GemmEpi& ep) {
-  float* p = C + (long long)row * ldc + col;
-  float z = accumulate ? *p + v : v;
-  if (ep.bias) z += ep.bias[col];
-  *p = z;
-  if (ep.act) ep.act[(long long)row * ep.ld_act + col] = f2bf(ep.gelu_on ? gelu(z) : z);
-}
-
 // ---------------------------------------------------------------------------
-// GEMM.  Block = 4 waves in a 2 x 2 arrangement, each wave a 32 x 32 tile of
+// The plain GEMM entry point (any strides).  Block = 4 waves in a 2 x 2 arrangement, each wave a 32 x 32 tile of
 // C (one 32x32x16 MFMA per K step of 16).  Operand layout of the MFMA
 // (measured on gfx950): lane l holds A[l%32][8(l/32) + e] and
 // B[8(l/32) + e][l%32], e = 0..7; accumulator register v of lane l holds
@@ -72,7 +63,7 @@ __device__ __forceinline__ void gemm_store(float* C, long long ldc, int row, int
 __global__ __launch_bounds__(256) void k_gemm_bf16(int M, int N, int K, int kper, const uint16_t* __restrict__ A,
                                                   long long a_rs, long long a_cs, const uint16_t* __restrict__ B,
                                                   long long b_rs, long long b_cs, float* __restrict__ C, long long ldc,
-                                                  int accumulate, float* __restrict__ W, GemmEpi ep) {
+                                                  int accumulate, float* __restrict__ W) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int li = lane & 31, lh = lane >> 5;
   const int i0 = blockIdx.x * 64 + (wv & 1) * 32;
@@ -144,82 +135,339 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(int M, int N, int K, int kper
     const int col = j0 + li;
     if (row < M && col < N) {
       if (Wz) Wz[(size_t)row * N + col] = acc[v];
-      else gemm_store(C, ldc, row, col, acc[v], accumulate, ep);
+      else C[(long long)row * ldc + col] = accumulate ? C[(long long)row * ldc + col] + acc[v] : acc[v];
     }
   }
 }
 
-// C (+)= sum over z = 0..S-1 of W[z] (M x N each), in that order, then the epilogue
+// C (+)= sum over z = 0..S-1 of W[z] (M x N each), in that order
 __global__ void k_splitk_reduce(int M, int N, int S, const float* __restrict__ W, float* __restrict__ C, long long ldc,
-                                int accumulate, GemmEpi ep) {
+                                int accumulate) {
   const long long total = (long long)M * N;
   for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
     float sum = W[t];
     for (int z = 1; z < S; ++z) sum += W[(size_t)z * total + t];
-    gemm_store(C, ldc, (int)(t / N), (int)(t % N), sum, accumulate, ep);
+    float* p = C + (t / N) * ldc + t % N;
+    *p = accumulate ? *p + sum : sum;
   }
 }
 
 // ---------------------------------------------------------------------------
-// elementwise pieces
+// The network's GEMMs.  A job is C (M x N) = A B^T over K-contiguous operands
+// (A[i lda + k], B[j ldb + k], K and both ld multiples of 8) in 32 x 32 tiles;
+// S waves of a block share a tile's K (slices of whole 16-steps, as many as
+// gemm_splits gives), their partial tiles are added through LDS in slice order,
+// and the job's epilogue runs on the sums.  A block of NW waves takes NW / S
+// tiles; a launch takes up to two jobs and the column sums of one bias gradient.
+// At these sizes (a 512 x 512 output is 256 tiles) a launch is bound by its chain
+// of latencies: few k-steps a wave, all of its loads in flight at once.
 // ---------------------------------------------------------------------------
-// dst (rows x cols_p, BF16) <- (src - mean) * inv_std (rows x cols, FP32), zero padding
-__global__ void k_to_bf16_pad(int rows, int cols, int cols_p, const float* __restrict__ src, const float* __restrict__ mean,
-                              const float* __restrict__ inv_std, uint16_t* __restrict__ dst) {
-  const long long total = (long long)rows * cols_p;
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int r = (int)(t / cols_p), c = (int)(t % cols_p);
-    dst[t] = c < cols ? f2bf((src[(long long)r * cols + c] - mean[c]) * inv_std[c]) : (uint16_t)0;
+enum { HM_HIDDEN, HM_OUT, HM_BACK, HM_WGRAD };
+struct MlpJob {
+  int kind = HM_WGRAD;
+  int M = 0, N = 0, K = 0, S = 1, kper = 0, tiles_m = 0, tiles = 0, blocks = 0;
+  const uint16_t *A = nullptr, *B = nullptr;
+  int lda = 0, ldb = 0;
+  // epilogue, by kind:
+  //  HIDDEN  Z = sum + bias; act = BF16(GELU(Z)), actT its transpose
+  //  OUT     Z = sum + bias (standardized output); user = out_mean + out_sd Z;
+  //          or the warm start; or the loss and its gradient dY (gf, act, actT)
+  //  BACK    dA = sum; gf = dA GELU'(Z), act and actT its BF16 copies
+  //  WGRAD   C = sum, C2 too if given
+  float *C = nullptr, *C2 = nullptr, *Z = nullptr, *gf = nullptr;
+  uint16_t *act = nullptr, *actT = nullptr;
+  const float* bias = nullptr;
+  int ld = 0, ldt = 0;    // leading dimensions of C / Z / gf / act, and of actT (rows M .. ldt - 1 are zeroed)
+};
+struct MlpOut {           // the OUT epilogue's data
+  const float *mean = nullptr, *sd = nullptr, *istd = nullptr;
+  float* user = nullptr;                                   // batch x N
+  const double *L = nullptr, *U = nullptr;                 // warm start (w0 given)
+  double *y0 = nullptr, *w0 = nullptr, *x0 = nullptr;
+  int* bad = nullptr;
+  float* score = nullptr;
+  int n = 0, m = 0;
+  const float *T = nullptr, *w = nullptr;                  // loss (T given)
+  float* Tstd = nullptr;
+  double* partial = nullptr;                               // one per block
+};
+struct ColSum { const float* dZ = nullptr; float *db = nullptr, *db2 = nullptr; int B = 0, N = 0, ld = 0, blocks = 0; };
+struct MlpLaunch { MlpJob job[2]; MlpOut out; ColSum cs; };
+
+#define HM_PITCH 33
+#define HM_SLAB 64     // K of a slab: one 128-byte line of every row
+#define HM_RING 3      // slabs in flight
+
+// Partial tile of a wave: MFMAs over the k-steps of [kbeg, kend), in order.  A
+// slab of 32 rows x 64 k of each operand is loaded line by line (8 rows a load, 16
+// bytes a lane; loading MFMA fragments directly touches 32 lines a load, and
+// eight waves then refetch every line four times through the L1), passes
+// through the wave's own LDS, its 16-byte chunks swizzled by row so that neither
+// side has bank conflicts, and is read back as fragments.  Loads run HM_RING
+// slabs ahead.
+__device__ __forceinline__ hm_f32x16 mlp_tile(const MlpJob& J, int i0, int j0, int kbeg, int kend, hm_u16x8* lds) {
+  const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5, lr = lane >> 3, lc = lane & 7;
+  const uint16_t *Ar[4], *Br[4];   // the lane's rows (past the edge: clamped, not stored)
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    Ar[q] = J.A + (long long)min(i0 + lr + 8 * q, J.M - 1) * J.lda;
+    Br[q] = J.B + (long long)min(j0 + lr + 8 * q, J.N - 1) * J.ldb;
   }
-}
-// T (rows x cols) -> (T - mean) * inv_std
-__global__ void k_standardize(int rows, int cols, const float* __restrict__ src, const float* __restrict__ mean,
-                              const float* __restrict__ inv_std, float* __restrict__ dst) {
-  const long long total = (long long)rows * cols;
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int c = (int)(t % cols);
-    dst[t] = (src[t] - mean[c]) * inv_std[c];
+  hm_f32x16 acc = {};
+  hm_u16x8 a[HM_RING][4], b[HM_RING][4];
+  auto load = [&](int s, int k0) {
+    const int kb = min(k0 + 8 * lc, kend - 8);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[s][q] = *reinterpret_cast<const hm_u16x8*>(Ar[q] + kb);
+      b[s][q] = *reinterpret_cast<const hm_u16x8*>(Br[q] + kb);
+    }
+  };
+  auto mul = [&](int s, int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      lds[(lr + 8 * q) * 8 + (lc ^ lr)] = a[s][q];
+      lds[256 + (lr + 8 * q) * 8 + (lc ^ lr)] = b[s][q];
+    }
+    hm_u16x8 fa[4], fb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      fa[u] = lds[li * 8 + ((2 * u + lh) ^ (li & 7))];
+      fb[u] = lds[256 + li * 8 + ((2 * u + lh) ^ (li & 7))];
+    }
+    const bool part = k0 + HM_SLAB > kend;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (part) {
+        if (k0 + 16 * u >= kend) break;
+        if (k0 + 16 * u + 8 >= kend && lh) { fa[u] = hm_u16x8{}; fb[u] = hm_u16x8{}; }   // half a step left
+      }
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(hm_bf16x8, fa[u]),
+                                                    __builtin_bit_cast(hm_bf16x8, fb[u]), acc, 0, 0, 0);
+    }
+  };
+  // (a slab past the end is the last entries again, unused)
+#pragma unroll
+  for (int s = 0; s < HM_RING; ++s)
+    if (kbeg + s * HM_SLAB < kend) load(s, kbeg + s * HM_SLAB);
+  int k0 = kbeg;
+  for (; k0 + HM_RING * HM_SLAB < kend; k0 += HM_RING * HM_SLAB) {
+#pragma unroll
+    for (int s = 0; s < HM_RING; ++s) {
+      mul(s, k0 + s * HM_SLAB);
+      load(s, k0 + (s + HM_RING) * HM_SLAB);
+    }
   }
+#pragma unroll
+  for (int s = 0; s < HM_RING; ++s)
+    if (k0 + s * HM_SLAB < kend) mul(s, k0 + s * HM_SLAB);
+  return acc;
 }
-// network output (standardized, ld) -> FP32 user units: mean + std * Y
-__global__ void k_destandardize(int rows, int cols, const float* __restrict__ Y, long long ld, const float* __restrict__ mean,
-                                const float* __restrict__ sd, float* __restrict__ out) {
-  const long long total = (long long)rows * cols;
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int r = (int)(t / cols), c = (int)(t % cols);
-    out[t] = mean[c] + sd[c] * Y[(long long)r * ld + c];
+
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_mlp_gemm(MlpLaunch p) {
+  // the waves' operand slabs, then the partial tiles and the tiles to transpose
+  __shared__ hm_u16x8 slab[NW][512];
+  static_assert(sizeof(slab[0]) >= 32 * HM_PITCH * sizeof(float) + 32 * (HM_PITCH + 1) * sizeof(uint16_t), "reuse");
+  float (*const part)[32 * HM_PITCH] = reinterpret_cast<float (*)[32 * HM_PITCH]>(&slab[0][0]);
+  uint16_t (*const tr)[32 * (HM_PITCH + 1)] = reinterpret_cast<uint16_t (*)[32 * (HM_PITCH + 1)]>(part + NW);
+  const int t = threadIdx.x, lane = t & 63;
+  int blk = blockIdx.x;
+  if (blk >= p.job[0].blocks + p.job[1].blocks) {
+    // db[j] = sum_b dZ[b][j]: 8 NW columns a block, thread (g, c) summing rows g,
+    // g + 8, ... of its column in FP64, the 8 sums of a column added in order
+    constexpr int CW = 8 * NW;
+    double* const ps = reinterpret_cast<double*>(&slab[0][0]);
+    const int c = t % CW, g = t / CW, j = (blk - p.job[0].blocks - p.job[1].blocks) * CW + c;
+    double s = 0.0;
+    if (j < p.cs.N) {
+#pragma unroll 8
+      for (int b = g; b < p.cs.B; b += 8) s += p.cs.dZ[(long long)b * p.cs.ld + j];
+    }
+    ps[g * CW + c] = s;
+    __syncthreads();
+    if (g == 0 && j < p.cs.N) {
+      double r = ps[c];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) r += ps[q * CW + c];
+      p.cs.db[j] = (float)r;
+      if (p.cs.db2) p.cs.db2[j] = (float)r;
+    }
+    return;
   }
-}
-// prediction [y (m); z (n); w (n) (; ell)] per sample (row length no) -> FP64
-// warm start of HPR-QP: y0 = y, w0 = w, x0 = Pi_C(w) (z is not read by the
-// iteration).  bad[s] = 1 if a predicted value of y or w is not finite: that
-// sample's start is then the origin (y0 = w0 = x0 = 0, the cold start of
-// Algorithm 4).  score (if given): the predicted length ell of each solve.
-__global__ void k_warm_start(int batch, int n, int m, int no, const float* __restrict__ P, const double* __restrict__ L,
-                             const double* __restrict__ U, double* __restrict__ y0, double* __restrict__ w0,
-                             double* __restrict__ x0, int* __restrict__ bad, float* __restrict__ score) {
-  const int s = blockIdx.x;
-  if (s >= batch) return;
-  const float* p = P + (long long)s * no;
-  int nf = 0;
-  for (int i = threadIdx.x; i < m; i += blockDim.x) nf |= !isfinite(p[i]);
-  for (int j = threadIdx.x; j < n; j += blockDim.x) nf |= !isfinite(p[m + n + j]);
-  __shared__ int sbad;
-  if (threadIdx.x == 0) sbad = 0;
+  const bool second = blk >= p.job[0].blocks;
+  if (second) blk -= p.job[0].blocks;
+  const MlpJob& J = p.job[second ? 1 : 0];
+  const int S = J.S, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int tt = wv / S, tile = blk * (NW / S) + tt;   // the wave's tile, in its products and its epilogue
+  const int i0 = (tile % J.tiles_m) * 32, j0 = (tile / J.tiles_m) * 32;
+  // epilogue: 64 S threads per tile, thread tl taking column tl % 32 of rows
+  // tl / 32, tl / 32 + 2 S, ...: its operands are loaded before the products
+  const int P = 64 * S, tl = t - tt * P, c = tl & 31, col = j0 + c;
+  const bool cin = tile < J.tiles && col < J.N;
+  const MlpOut& o = p.out;
+  const bool lossy = J.kind == HM_OUT && o.T != nullptr;
+  float cb = 0.0f, cm = 0.0f, cs = 0.0f, ci = 0.0f, cw = 1.0f, er[16];
+  double cL = 0.0, cU = 0.0;
+  if (cin && J.bias) cb = J.bias[col];
+  if (cin && J.kind == HM_OUT) {
+    cm = o.mean[col]; cs = o.sd[col]; ci = o.istd[col];
+    if (o.w) cw = o.w[col];
+    if (o.w0 && col >= o.m + o.n && col < o.m + 2 * o.n) { cL = o.L[col - o.m - o.n]; cU = o.U[col - o.m - o.n]; }
+  }
+  const float* const ex = lossy ? o.T : J.kind == HM_BACK ? J.Z : nullptr;   // one operand per element
+  const long long ex_ld = lossy ? J.N : J.ld;
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+    if (ex && q * P < 1024) {
+      const int row = i0 + ((tl + q * P) >> 5);
+      er[q] = cin && row < J.M ? ex[row * ex_ld + col] : 0.0f;
+    }
+  {
+    const int z = wv % S, kbeg = z * J.kper, kend = min(J.K, kbeg + J.kper);
+    const bool work = tile < J.tiles && kbeg < kend;
+    hm_f32x16 acc = {};
+    if (work) acc = mlp_tile(J, i0, j0, kbeg, kend, slab[wv]);
+    __syncthreads();   // the slabs' memory holds the partial tiles now
+    if (work) {
+      const int li = lane & 31, lh = lane >> 5;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[wv][(8 * (v >> 2) + 4 * lh + (v & 3)) * HM_PITCH + li] = acc[v];
+    }
+  }
   __syncthreads();
-  if (nf) atomicOr(&sbad, 1);
+  const int nz = (J.K + J.kper - 1) / J.kper;
+  const double scale = lossy ? 1.0 / ((double)J.M * (double)J.N) : 0.0;
+  const float gscale = (float)(2.0 * scale);
+  double lacc = 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    if (q * P >= 1024) break;
+    const int r = (tl + q * P) >> 5, row = i0 + r;
+    uint16_t hb = 0;
+    if (cin && row < J.M) {
+      float v = part[tt * S][r * HM_PITCH + c];
+      for (int z = 1; z < nz; ++z) v += part[tt * S + z][r * HM_PITCH + c];
+      const long long at = (long long)row * J.ld + col;
+      switch (J.kind) {
+        case HM_HIDDEN: {
+          v += cb;
+          J.Z[at] = v;
+          hb = f2bf(gelu(v));
+          J.act[at] = hb;
+          break;
+        }
+        case HM_OUT: {
+          v += cb;
+          J.Z[at] = v;
+          if (o.user) o.user[(long long)row * J.N + col] = __builtin_fmaf(cs, v, cm);
+          if (o.w0) {
+            // prediction [y (m); z (n); w (n) (; ell)] -> FP64 start; z is not read by the iteration
+            const float f = __builtin_fmaf(cs, v, cm);
+            const int m = o.m, n = o.n, j = col - m - n;
+            if (col < m) {
+              if (!isfinite(f)) atomicOr(o.bad + row, 1);
+              o.y0[(long long)row * m + col] = (double)f;
+            } else if (j >= 0 && j < n) {
+              if (!isfinite(f)) atomicOr(o.bad + row, 1);
+              o.w0[(long long)row * n + j] = (double)f;
+              o.x0[(long long)row * n + j] = fmin(fmax((double)f, cL), cU);
+            } else if (j == n && o.score) {
+              o.score[row] = f;
+            }
+          }
+          if (lossy) {
+            // weighted MSE: dY = 2 w (Y - T) / (B N).  The standardized target is
+            // rounded before the difference (the empty asm keeps them apart).
+            float ts = (er[q] - cm) * ci;
+            asm volatile("" : "+v"(ts));
+            o.Tstd[(long long)row * J.N + col] = ts;
+            const float d = v - ts;
+            lacc += (double)cw * (double)d * (double)d;
+            const float g = gscale * cw * d;
+            J.gf[at] = g;
+            hb = f2bf(g);
+            J.act[at] = hb;
+          }
+          break;
+        }
+        case HM_BACK: {
+          J.C[at] = v;
+          const float g = v * gelu_d(er[q]);
+          J.gf[at] = g;
+          hb = f2bf(g);
+          J.act[at] = hb;
+          break;
+        }
+        default: {
+          J.C[at] = v;
+          if (J.C2) J.C2[at] = v;
+        }
+      }
+    }
+    if (J.actT) tr[tt][c * (HM_PITCH + 1) + r] = hb;
+  }
+  if (J.actT) {
+    __syncthreads();
+    if (tile < J.tiles)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        if (q * P >= 1024) break;
+        const int cc = (tl + q * P) >> 5, r = tl & 31;
+        if (j0 + cc < J.N && i0 + r < J.ldt)
+          J.actT[(long long)(j0 + cc) * J.ldt + i0 + r] = tr[tt][cc * (HM_PITCH + 1) + r];
+      }
+  }
+  if (lossy) {
+    double* const ps = reinterpret_cast<double*>(&slab[0][0]);
+    for (int off = 32; off; off >>= 1) lacc += __shfl_xor(lacc, off);
+    __syncthreads();
+    if (lane == 0) ps[wv] = lacc;
+    __syncthreads();
+    if (t == 0) {
+      double s = ps[0];
+      for (int w = 1; w < NW; ++w) s += ps[w];
+      o.partial[blk] = s * scale;
+    }
+  }
+}
+
+// Network input: Xb (rows x cols_p, BF16) <- (X - mean) * inv_std, zero padding,
+// and its transpose Xt (cols_p x rows_p) if given; clears `bad` (rows) if given.
+// One 32 x 32 tile per block.
+__global__ __launch_bounds__(256) void k_mlp_input(int rows, int rows_p, int cols, int cols_p, const float* __restrict__ X,
+                                                   const float* __restrict__ mean, const float* __restrict__ inv_std,
+                                                   uint16_t* __restrict__ Xb, uint16_t* __restrict__ Xt,
+                                                   int* __restrict__ bad) {
+  __shared__ uint16_t tile[32][33];
+  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
+  const int c = c0 + tx;
+  const float mu = c < cols ? mean[c] : 0.0f, is = c < cols ? inv_std[c] : 0.0f;
+#pragma unroll
+  for (int y = ty; y < 32; y += 8) {
+    const int r = r0 + y;
+    uint16_t u = 0;
+    if (r < rows && c < cols) u = f2bf((X[(long long)r * cols + c] - mu) * is);
+    if (r < rows && c < cols_p) Xb[(long long)r * cols_p + c] = u;
+    if (Xt) tile[y][tx] = u;
+  }
+  if (bad && blockIdx.x == 0 && threadIdx.x < 32 && r0 + (int)threadIdx.x < rows) bad[r0 + threadIdx.x] = 0;
+  if (!Xt) return;
   __syncthreads();
-  const bool cold = sbad != 0;
-  for (int i = threadIdx.x; i < m; i += blockDim.x) y0[(long long)s * m + i] = cold ? 0.0 : (double)p[i];
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    const double wv = cold ? 0.0 : (double)p[m + n + j];
-    w0[(long long)s * n + j] = wv;
-    x0[(long long)s * n + j] = cold ? 0.0 : fmin(fmax(wv, L[j]), U[j]);
-  }
-  if (threadIdx.x == 0) {
-    bad[s] = cold ? 1 : 0;
-    if (score) score[s] = p[m + 2 * n];
-  }
+#pragma unroll
+  for (int y = ty; y < 32; y += 8)
+    if (c0 + y < cols_p && r0 + tx < rows_p) Xt[(long long)(c0 + y) * rows_p + r0 + tx] = tile[tx][y];
+}
+
+// Samples whose predicted y or w is not finite start from the origin (the
+// cold start of Algorithm 4): bad[s] = 1
+__global__ __launch_bounds__(256) void k_warm_fix(int n, int m, const int* __restrict__ bad, double* __restrict__ y0,
+                                                  double* __restrict__ w0, double* __restrict__ x0) {
+  const long long s = blockIdx.x;
+  if (!bad[s]) return;
+  for (int i = threadIdx.x; i < m; i += blockDim.x) y0[s * m + i] = 0.0;
+  for (int j = threadIdx.x; j < n; j += blockDim.x) { w0[s * n + j] = 0.0; x0[s * n + j] = 0.0; }
 }
 
 // out (rows x cols, FP32) <- a stage tensor with leading dimension ld, FP32
@@ -292,110 +540,84 @@ __global__ void k_family_targets(int batch, int n, int m, const double* __restri
   }
 }
 
-// dst (cols_p x rows_p) = transpose of src (rows x cols_p), zero rows beyond `rows`
-__global__ void k_transpose_bf16(int rows, int rows_p, int cols_p, const uint16_t* __restrict__ src,
-                                 uint16_t* __restrict__ dst) {
+__device__ __forceinline__ float adam_step(float& p, float g, float& m, float& v, float lr, float b1, float b2,
+                                           float eps, float c1, float c2) {
+  const float mi = b1 * m + (1.0f - b1) * g;
+  const float vi = b2 * v + (1.0f - b2) * g * g;
+  m = mi; v = vi;
+  p -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  return p;
+}
+
+// One Adam step on every parameter, and the BF16 copies of the weights, Wb
+// (rows x cols_p) and its transpose Wt (cols x rows_p), from the tile just
+// updated.  Blocks take the 32 x 32 tiles of the three weight matrices, then the
+// biases.  (The copies' padding is zero from creation.)  step = 0: the copies only.
+struct AdamArgs {
+  float *p, *m, *v;
+  const float* g;
+  long long off_W[3], off_b[3];
+  int rows[3], cols[3], rows_p[3], cols_p[3], tiles[3];
+  uint16_t *Wb[3], *Wt[3];
+  float lr, b1, b2, eps, c1, c2;
+  int step;
+};
+__global__ __launch_bounds__(256) void k_adam(AdamArgs a) {
   __shared__ uint16_t tile[32][33];
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
-  for (int y = ty; y < 32; y += 8) {
-    const int r = r0 + y, c = c0 + tx;
-    tile[y][tx] = (r < rows && c < cols_p) ? src[(long long)r * cols_p + c] : (uint16_t)0;
-  }
-  __syncthreads();
-  for (int y = ty; y < 32; y += 8) {
-    const int c = c0 + y, r = r0 + tx;
-    if (c < cols_p && r < rows_p) dst[(long long)c * rows_p + r] = tile[tx][y];
-  }
-}
-
-
-// weighted MSE: dY = 2 w (Y - T)/(B N) (FP32 and BF16 copies), per-block loss partials
-__global__ __launch_bounds__(256) void k_mse(int B, int N, const float* __restrict__ Y, long long ldy,
-                                             const float* __restrict__ T, const float* __restrict__ w,
-                                             float* __restrict__ dYf, uint16_t* __restrict__ dYb, long long ldd,
-                                             double* __restrict__ partial) {
-  const double scale = 1.0 / ((double)B * (double)N);
-  double acc = 0.0;
-  const long long total = (long long)B * N;
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int b = (int)(t / N), j = (int)(t % N);
-    const float wj = w ? w[j] : 1.0f;
-    const float r = Y[(long long)b * ldy + j] - T[t];
-    acc += (double)wj * (double)r * (double)r;
-    const float g = (float)(2.0 * scale) * wj * r;
-    dYf[(long long)b * ldd + j] = g;
-    dYb[(long long)b * ldd + j] = f2bf(g);
-  }
-  __shared__ double sh[256];
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = sh[0] * scale;
-}
-
-// dZ = dA * GELU'(Z)
-__global__ void k_gelu_bwd(int B, int N, const float* __restrict__ dA, long long lda, const float* __restrict__ Z,
-                           long long ldz, float* __restrict__ dZf, uint16_t* __restrict__ dZb, long long ldo) {
-  const long long total = (long long)B * N;
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int b = (int)(t / N), j = (int)(t % N);
-    const float g = dA[(long long)b * lda + j] * gelu_d(Z[(long long)b * ldz + j]);
-    dZf[(long long)b * ldo + j] = g;
-    dZb[(long long)b * ldo + j] = f2bf(g);
-  }
-}
-
-// db[j] = sum_b dZ[b][j]: a block of 256 threads covers 32 columns, thread
-// (g, c) summing rows g, g + 8, ... of its column in FP64, and the 8 partial
-// sums of a column are added in the order g = 0..7 (deterministic; reading
-// rows 8 at a time keeps 8 loads per column in flight)
-#define HM_CS_COLS 32
-#define HM_CS_GRP 8
-__global__ __launch_bounds__(256) void k_colsum(int B, int N, const float* __restrict__ dZ, long long ld,
-                                                float* __restrict__ db) {
-  __shared__ double part[HM_CS_GRP][HM_CS_COLS];
-  const int c = threadIdx.x % HM_CS_COLS, g = threadIdx.x / HM_CS_COLS;
-  for (int j0 = blockIdx.x * HM_CS_COLS; j0 < N; j0 += gridDim.x * HM_CS_COLS) {
-    const int j = j0 + c;
-    double s = 0.0;
-    if (j < N)
-      for (int b = g; b < B; b += HM_CS_GRP) s += dZ[(long long)b * ld + j];
-    part[g][c] = s;
-    __syncthreads();
-    if (g == 0 && j < N) {
-      double t = part[0][c];
+  int blk = blockIdx.x;
 #pragma unroll
-      for (int q = 1; q < HM_CS_GRP; ++q) t += part[q][c];
-      db[j] = (float)t;
+  for (int l = 0; l < 3; ++l) {
+    if (blk < a.tiles[l]) {
+      const int tn = (a.cols[l] + 31) / 32, c0 = (blk % tn) * 32, r0 = (blk / tn) * 32;
+      const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+      const int c = c0 + tx;
+      float pv[4], gv[4], mv[4], vv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = r0 + ty + 8 * q;
+        if (r < a.rows[l] && c < a.cols[l]) {
+          const long long i = a.off_W[l] + (long long)r * a.cols[l] + c;
+          pv[q] = a.p[i];
+          if (a.step) { gv[q] = a.g[i]; mv[q] = a.m[i]; vv[q] = a.v[i]; }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = r0 + ty + 8 * q;
+        if (r < a.rows[l] && c < a.cols[l]) {
+          const long long i = a.off_W[l] + (long long)r * a.cols[l] + c;
+          if (a.step) {
+            a.p[i] = adam_step(pv[q], gv[q], mv[q], vv[q], a.lr, a.b1, a.b2, a.eps, a.c1, a.c2);
+            a.m[i] = mv[q]; a.v[i] = vv[q];
+          }
+          const uint16_t u = f2bf(pv[q]);
+          a.Wb[l][(long long)r * a.cols_p[l] + c] = u;
+          tile[ty + 8 * q][tx] = u;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int cc = c0 + ty + 8 * q, r = r0 + tx;
+        if (cc < a.cols[l] && r < a.rows[l]) a.Wt[l][(long long)cc * a.rows_p[l] + r] = tile[tx][ty + 8 * q];
+      }
+      return;
     }
-    __syncthreads();
+    blk -= a.tiles[l];
   }
-}
-
-__global__ void k_adam(long long n, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi; v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  }
-}
-
-// W (rows x cols, FP32 master) -> Wb (rows_p x cols_p, BF16) and Wt (cols_p x rows_p, BF16)
-__global__ void k_weights_bf16(int rows, int cols, int rows_p, int cols_p, const float* __restrict__ W,
-                               uint16_t* __restrict__ Wb, uint16_t* __restrict__ Wt) {
-  const long long total = (long long)rows_p * cols_p;
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int r = (int)(t / cols_p), c = (int)(t % cols_p);
-    const uint16_t u = (r < rows && c < cols) ? f2bf(W[(long long)r * cols + c]) : (uint16_t)0;
-    Wb[t] = u;
-    Wt[(long long)c * rows_p + r] = u;
+  if (!a.step) return;
+  // biases, one after the other in thread order
+  long long k = (long long)blk * 256 + threadIdx.x;
+#pragma unroll
+  for (int l = 0; l < 3; ++l) {
+    if (k < a.rows[l]) {
+      const long long i = a.off_b[l] + k;
+      float pv = a.p[i], mv = a.m[i], vv = a.v[i];
+      a.p[i] = adam_step(pv, a.g[i], mv, vv, a.lr, a.b1, a.b2, a.eps, a.c1, a.c2);
+      a.m[i] = mv; a.v[i] = vv;
+      return;
+    }
+    k -= a.rows[l];
   }
 }
 
@@ -416,15 +638,13 @@ struct hprqp_mlp {
   float *Z1 = nullptr, *Z2 = nullptr, *Y = nullptr;
   float *dYf = nullptr, *dA2 = nullptr, *dZ2f = nullptr, *dA1 = nullptr, *dZ1f = nullptr;
   uint16_t *dYb = nullptr, *dYt = nullptr, *dZ2b = nullptr, *dZ2t = nullptr, *dZ1b = nullptr, *dZ1t = nullptr;
-  double* part = nullptr;
-  float* ws = nullptr;          // split-K partials of the GEMMs
-  long long ws_floats = 0;
+  double* loss_part = nullptr;  // pinned host memory: the loss of each block of the output layer
   int ncu = 0;
   // input / output standardization (set by hprqp_mlp_set_scaling; identity by default)
   float *in_mean = nullptr, *in_istd = nullptr, *out_mean = nullptr, *out_sd = nullptr, *out_istd = nullptr;
-  float *Tstd = nullptr, *Yuser = nullptr;
+  float* Tstd = nullptr;
   std::vector<void*> owned;
-  hipEvent_t ev[16] = {};
+  hipEvent_t ev[4] = {};
   int nev = 0;
   double last_flop = 0.0;
   int last_batch = 0;   // batch of the last forward / loss_grad
@@ -432,6 +652,7 @@ struct hprqp_mlp {
     for (void* p : owned) hipFree(p);
     for (auto e : ev)
       if (e) hipEventDestroy(e);
+    if (loss_part) hipHostFree(loss_part);
     if (own_st) hipStreamDestroy(own_st);
   }
 };
@@ -450,67 +671,102 @@ void mcheck(hipError_t e, const char* w) {
 }
 #define HMC(x) mcheck((x), #x)
 
-template <class T>
-T* malloc_dev(hprqp_mlp& n, size_t count) {
-  void* p = nullptr;
-  HMC(hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T)));
-  HMC(hipMemsetAsync(p, 0, std::max<size_t>(count, 1) * sizeof(T), n.st));
-  n.owned.push_back(p);
-  return (T*)p;
-}
+// The handle's device arrays: asked for one by one, then taken (zeroed) from one
+// allocation
+struct Arena {
+  std::vector<std::pair<void**, size_t>> want;
+  size_t bytes = 0;
+  template <class T>
+  void add(T*& p, size_t count) {
+    want.emplace_back((void**)&p, bytes);
+    bytes += (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
+  }
+  void take(hprqp_mlp& n) {
+    void* base = nullptr;
+    HMC(hipMalloc(&base, bytes));
+    n.owned.push_back(base);
+    HMC(hipMemsetAsync(base, 0, bytes, n.st));
+    for (auto& w : want) *w.first = (char*)base + w.second;
+  }
+};
 
 int eg(long long work) {
   long long g = (work + 255) / 256;
   return (int)std::max(1LL, std::min(g, 4096LL));
 }
 
-int cs_grid(int cols) { return std::max(1, std::min((cols + HM_CS_COLS - 1) / HM_CS_COLS, 4096)); }
-
 // K splits of a GEMM: doubled while the launch holds fewer than 4 waves per
-// CU, each split keeps at least 4 k-steps of 16 and the partials fit the
-// workspace (the network's GEMMs are small: a 512 x 512 output is 64 tiles,
-// 256 waves, too few to hide the fragment loads on 256 CUs)
-int gemm_splits(int M, int N, int K, int ncu, long long ws_floats) {
-  const long long waves = 4LL * ((M + 63) / 64) * ((N + 63) / 64);
+// CU, each split keeps at least 4 k-steps of 16 and the partial products stay
+// below 32 Ki floats per CU (the network's GEMMs are small: a 512 x 512 output
+// is 64 tiles of 64 x 64, 256 waves, too few to hide the fragment loads on 256 CUs)
+int gemm_splits(int M, int N, int K, int ncu) {
+  const long long waves = 4LL * ((M + 63) / 64) * ((N + 63) / 64), most = 2LL * ncu * 4096 * 4;
   const int ksteps = (K + 15) / 16;
   int S = 1;
-  while (S < 8 && waves * S < 4LL * ncu && ksteps >= 8 * S && (long long)(2 * S) * M * N <= ws_floats) S *= 2;
+  while (S < 8 && waves * S < 4LL * ncu && ksteps >= 8 * S && (long long)(2 * S) * M * N <= most) S *= 2;
   return S;
 }
 
 // C (+)= A B with S K-splits (S > 1: the partials go through ws, which holds
 // at least S M N floats)
 void gemm_split(hipStream_t st, int M, int N, int K, const uint16_t* A, long long a_rs, long long a_cs,
-                const uint16_t* B, long long b_rs, long long b_cs, float* C, long long ldc, int acc, int S, float* ws,
-                const GemmEpi& ep = GemmEpi{}) {
+                const uint16_t* B, long long b_rs, long long b_cs, float* C, long long ldc, int acc, int S, float* ws) {
   const int ksteps = (K + 15) / 16;
   if (S < 1) S = 1;
   const int kper = 16 * ((ksteps + S - 1) / S);
   const int Se = kper > 0 ? (K + kper - 1) / kper : 1;
   if (Se <= 1) {
     dim3 grid((M + 63) / 64, (N + 63) / 64, 1);
-    k_gemm_bf16<<<grid, 256, 0, st>>>(M, N, K, std::max(kper, 16), A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, acc, nullptr,
-                                      ep);
+    k_gemm_bf16<<<grid, 256, 0, st>>>(M, N, K, std::max(kper, 16), A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, acc, nullptr);
     return;
   }
   dim3 grid((M + 63) / 64, (N + 63) / 64, Se);
-  k_gemm_bf16<<<grid, 256, 0, st>>>(M, N, K, kper, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, acc, ws, GemmEpi{});
-  k_splitk_reduce<<<eg((long long)M * N), 256, 0, st>>>(M, N, Se, ws, C, ldc, acc, ep);
+  k_gemm_bf16<<<grid, 256, 0, st>>>(M, N, K, kper, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, acc, ws);
+  k_splitk_reduce<<<eg((long long)M * N), 256, 0, st>>>(M, N, Se, ws, C, ldc, acc);
 }
 
-// a GEMM of the network: K split by gemm_splits, partials in the handle's workspace
-void gemm(hprqp_mlp& n, int M, int N, int K, const uint16_t* A, long long a_rs, long long a_cs, const uint16_t* B,
-          long long b_rs, long long b_cs, float* C, long long ldc, int acc, const GemmEpi& ep = GemmEpi{}) {
-  gemm_split(n.st, M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, acc, gemm_splits(M, N, K, n.ncu, n.ws_floats), n.ws,
-             ep);
+// a job of the network: operands and shape; the caller fills in the epilogue
+MlpJob job(const hprqp_mlp& n, int kind, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb) {
+  MlpJob J;
+  J.kind = kind; J.M = M; J.N = N; J.K = K;
+  J.A = A; J.lda = lda; J.B = B; J.ldb = ldb;
+  J.S = gemm_splits(M, N, K, n.ncu);
+  J.kper = 16 * (((K + 15) / 16 + J.S - 1) / J.S);
+  J.tiles_m = (M + 31) / 32;
+  J.tiles = J.tiles_m * ((N + 31) / 32);
+  return J;
+}
+ColSum colsum(int B, int N, const float* dZ, int ld, float* db, float* db2) {
+  ColSum c;
+  c.B = B; c.N = N; c.dZ = dZ; c.ld = ld; c.db = db; c.db2 = db2;
+  return c;
+}
+// Waves per block: 8 where a tile's K is shared by 8, else 4 (more blocks: the
+// output layer at batch 512 is 1024 tiles).  Returns the first job's blocks.
+int launch(hprqp_mlp& n, MlpLaunch p) {
+  const int NW = p.job[0].S == 8 || p.job[1].S == 8 ? 8 : 4;
+  for (MlpJob& J : p.job) J.blocks = (J.tiles * J.S + NW - 1) / NW;
+  p.cs.blocks = (p.cs.N + 8 * NW - 1) / (8 * NW);
+  const int grid = p.job[0].blocks + p.job[1].blocks + p.cs.blocks;
+  if (NW == 8) k_mlp_gemm<8><<<grid, 512, 0, n.st>>>(p);
+  else k_mlp_gemm<4><<<grid, 256, 0, n.st>>>(p);
+  return p.job[0].blocks;
 }
 
-void refresh_weights(hprqp_mlp& n) {
+AdamArgs adam_args(hprqp_mlp& n) {
+  AdamArgs a{};
+  a.p = n.P; a.m = n.Mm; a.v = n.Vv; a.g = n.G;
   for (int l = 0; l < 3; ++l) {
-    const int rows = n.d[l + 1], cols = n.d[l], rows_p = n.dp[l + 1], cols_p = n.dp[l];
-    k_weights_bf16<<<eg((long long)rows_p * cols_p), 256, 0, n.st>>>(rows, cols, rows_p, cols_p, n.P + n.off_W[l],
-                                                                    n.Wb[l], n.Wt[l]);
+    a.off_W[l] = n.off_W[l]; a.off_b[l] = n.off_b[l];
+    a.rows[l] = n.d[l + 1]; a.cols[l] = n.d[l]; a.rows_p[l] = n.dp[l + 1]; a.cols_p[l] = n.dp[l];
+    a.tiles[l] = ((a.rows[l] + 31) / 32) * ((a.cols[l] + 31) / 32);
+    a.Wb[l] = n.Wb[l]; a.Wt[l] = n.Wt[l];
   }
+  return a;
+}
+void refresh_weights(hprqp_mlp& n) {
+  const AdamArgs a = adam_args(n);
+  k_adam<<<a.tiles[0] + a.tiles[1] + a.tiles[2], 256, 0, n.st>>>(a);
 }
 
 void create_impl(const int32_t dims[4], int32_t max_batch, const float* params_host, hipStream_t st, hprqp_mlp** out) {
@@ -534,53 +790,52 @@ void create_impl(const int32_t dims[4], int32_t max_batch, const float* params_h
       n->off_b[l] = o; o += n->d[l + 1];
     }
     n->np = o;
-    n->P = malloc_dev<float>(*n, o);
-    n->G = malloc_dev<float>(*n, o);
-    n->Mm = malloc_dev<float>(*n, o);
-    n->Vv = malloc_dev<float>(*n, o);
-    if (params_host) HMC(hipMemcpyAsync(n->P, params_host, o * sizeof(float), hipMemcpyHostToDevice, st));
+    Arena mem;
+    mem.add(n->P, o);
+    mem.add(n->G, o);
+    mem.add(n->Mm, o);
+    mem.add(n->Vv, o);
     for (int l = 0; l < 3; ++l) {
-      n->Wb[l] = malloc_dev<uint16_t>(*n, (size_t)n->dp[l + 1] * n->dp[l]);
-      n->Wt[l] = malloc_dev<uint16_t>(*n, (size_t)n->dp[l + 1] * n->dp[l]);
+      mem.add(n->Wb[l], (size_t)n->dp[l + 1] * n->dp[l]);
+      mem.add(n->Wt[l], (size_t)n->dp[l + 1] * n->dp[l]);
     }
     const size_t B = n->maxbp;
-    n->Xb = malloc_dev<uint16_t>(*n, B * n->dp[0]);
-    n->Xt = malloc_dev<uint16_t>(*n, B * n->dp[0]);
-    n->A1b = malloc_dev<uint16_t>(*n, B * n->dp[1]);
-    n->A1t = malloc_dev<uint16_t>(*n, B * n->dp[1]);
-    n->A2b = malloc_dev<uint16_t>(*n, B * n->dp[2]);
-    n->A2t = malloc_dev<uint16_t>(*n, B * n->dp[2]);
-    n->Z1 = malloc_dev<float>(*n, B * n->dp[1]);
-    n->Z2 = malloc_dev<float>(*n, B * n->dp[2]);
-    n->Y = malloc_dev<float>(*n, B * n->dp[3]);
-    n->dYf = malloc_dev<float>(*n, B * n->dp[3]);
-    n->dYb = malloc_dev<uint16_t>(*n, B * n->dp[3]);
-    n->dYt = malloc_dev<uint16_t>(*n, B * n->dp[3]);
-    n->dA2 = malloc_dev<float>(*n, B * n->dp[2]);
-    n->dZ2f = malloc_dev<float>(*n, B * n->dp[2]);
-    n->dZ2b = malloc_dev<uint16_t>(*n, B * n->dp[2]);
-    n->dZ2t = malloc_dev<uint16_t>(*n, B * n->dp[2]);
-    n->dA1 = malloc_dev<float>(*n, B * n->dp[1]);
-    n->dZ1f = malloc_dev<float>(*n, B * n->dp[1]);
-    n->dZ1b = malloc_dev<uint16_t>(*n, B * n->dp[1]);
-    n->dZ1t = malloc_dev<uint16_t>(*n, B * n->dp[1]);
-    n->part = malloc_dev<double>(*n, 4096);
+    mem.add(n->Xb, B * n->dp[0]);
+    mem.add(n->Xt, B * n->dp[0]);
+    mem.add(n->A1b, B * n->dp[1]);
+    mem.add(n->A1t, B * n->dp[1]);
+    mem.add(n->A2b, B * n->dp[2]);
+    mem.add(n->A2t, B * n->dp[2]);
+    mem.add(n->Z1, B * n->dp[1]);
+    mem.add(n->Z2, B * n->dp[2]);
+    mem.add(n->Y, B * n->dp[3]);
+    mem.add(n->dYf, B * n->dp[3]);
+    mem.add(n->dYb, B * n->dp[3]);
+    mem.add(n->dYt, B * n->dp[3]);
+    mem.add(n->dA2, B * n->dp[2]);
+    mem.add(n->dZ2f, B * n->dp[2]);
+    mem.add(n->dZ2b, B * n->dp[2]);
+    mem.add(n->dZ2t, B * n->dp[2]);
+    mem.add(n->dA1, B * n->dp[1]);
+    mem.add(n->dZ1f, B * n->dp[1]);
+    mem.add(n->dZ1b, B * n->dp[1]);
+    mem.add(n->dZ1t, B * n->dp[1]);
     {
       int dev = 0;
       HMC(hipGetDevice(&dev));
       HMC(hipDeviceGetAttribute(&n->ncu, hipDeviceAttributeMultiprocessorCount, dev));
-      // split-K partials: gemm_splits only splits launches of fewer than 4
-      // waves per CU, whose partials stay well below this; beyond it, fewer splits
-      n->ws_floats = 2LL * n->ncu * 4096 * 4;
-      n->ws = malloc_dev<float>(*n, (size_t)n->ws_floats);
+      // at most one block per tile of the output layer
+      const size_t most = ((B + 31) / 32) * ((size_t)(n->d[3] + 31) / 32);
+      HMC(hipHostMalloc((void**)&n->loss_part, most * sizeof(double), hipHostMallocDefault));
     }
-    n->in_mean = malloc_dev<float>(*n, n->d[0]);
-    n->in_istd = malloc_dev<float>(*n, n->d[0]);
-    n->out_mean = malloc_dev<float>(*n, n->d[3]);
-    n->out_sd = malloc_dev<float>(*n, n->d[3]);
-    n->out_istd = malloc_dev<float>(*n, n->d[3]);
-    n->Tstd = malloc_dev<float>(*n, (size_t)n->maxb * n->d[3]);
-    n->Yuser = malloc_dev<float>(*n, (size_t)n->maxb * n->d[3]);
+    mem.add(n->in_mean, n->d[0]);
+    mem.add(n->in_istd, n->d[0]);
+    mem.add(n->out_mean, n->d[3]);
+    mem.add(n->out_sd, n->d[3]);
+    mem.add(n->out_istd, n->d[3]);
+    mem.add(n->Tstd, (size_t)n->maxb * n->d[3]);
+    mem.take(*n);
+    if (params_host) HMC(hipMemcpyAsync(n->P, params_host, o * sizeof(float), hipMemcpyHostToDevice, st));
     {
       std::vector<float> ones(std::max(n->d[0], n->d[3]), 1.0f);
       HMC(hipMemcpyAsync(n->in_istd, ones.data(), n->d[0] * sizeof(float), hipMemcpyHostToDevice, st));
@@ -600,77 +855,91 @@ void create_impl(const int32_t dims[4], int32_t max_batch, const float* params_h
 
 void mark(hprqp_mlp& n) { HMC(hipEventRecord(n.ev[n.nev++], n.st)); }
 
-void forward_impl(hprqp_mlp& n, int B, const float* X) {
+// Forward pass; `out`: what the output layer's epilogue makes of its result.
+// train: the transposed copies and the loss (its partials in n.loss_part, one per
+// block of the returned count).
+int forward_impl(hprqp_mlp& n, int B, const float* X, const MlpOut& out) {
   if (B <= 0 || B > n.maxb || !X) mfail(HPRQP_ERR_ARG, "batch out of range or NULL input");
   n.last_batch = B;
-  const int in = n.d[0], h1 = n.d[1], h2 = n.d[2], out = n.d[3];
+  const bool train = out.T != nullptr;
+  const int in = n.d[0], h1 = n.d[1], h2 = n.d[2], no = n.d[3];
   const int inp = n.dp[0], h1p = n.dp[1], h2p = n.dp[2], outp = n.dp[3];
-  k_to_bf16_pad<<<eg((long long)B * inp), 256, 0, n.st>>>(B, in, inp, X, n.in_mean, n.in_istd, n.Xb);
+  const int Bp = rup8(B);
+  k_mlp_input<<<dim3((inp + 31) / 32, (Bp + 31) / 32), 256, 0, n.st>>>(B, Bp, in, inp, X, n.in_mean, n.in_istd, n.Xb,
+                                                                      train ? n.Xt : nullptr, out.bad);
   n.nev = 0;
   mark(n);
-  // each layer: Z = W x + b, then the hidden layers' GELU to BF16, in the GEMM's epilogue
-  gemm(n, B, h1, inp, n.Xb, inp, 1, n.Wb[0], 1, inp, n.Z1, h1p, 0, GemmEpi{n.P + n.off_b[0], n.A1b, h1p, 1});
+  auto hidden = [&](MlpJob J, float* Z, uint16_t* act, uint16_t* actT, const float* bias, int ld) {
+    J.Z = Z; J.act = act; J.actT = train ? actT : nullptr; J.bias = bias; J.ld = ld; J.ldt = Bp;
+    MlpLaunch p;
+    p.job[0] = J;
+    launch(n, p);
+  };
+  hidden(job(n, HM_HIDDEN, B, h1, inp, n.Xb, inp, n.Wb[0], inp), n.Z1, n.A1b, n.A1t, n.P + n.off_b[0], h1p);
+  hidden(job(n, HM_HIDDEN, B, h2, h1p, n.A1b, h1p, n.Wb[1], h1p), n.Z2, n.A2b, n.A2t, n.P + n.off_b[1], h2p);
+  MlpLaunch p;
+  p.out = out;
+  p.out.mean = n.out_mean; p.out.sd = n.out_sd; p.out.istd = n.out_istd;
+  p.out.Tstd = n.Tstd;
+  p.out.partial = n.loss_part;
+  MlpJob J = job(n, HM_OUT, B, no, h2p, n.A2b, h2p, n.Wb[2], h2p);
+  J.Z = n.Y; J.bias = n.P + n.off_b[2]; J.ld = outp;
+  J.gf = n.dYf; J.act = n.dYb; J.actT = train ? n.dYt : nullptr; J.ldt = Bp;
+  p.job[0] = J;
+  const int parts = launch(n, p);
   mark(n);
-  mark(n);
-  gemm(n, B, h2, h1p, n.A1b, h1p, 1, n.Wb[1], 1, h1p, n.Z2, h2p, 0, GemmEpi{n.P + n.off_b[1], n.A2b, h2p, 1});
-  mark(n);
-  mark(n);
-  gemm(n, B, out, h2p, n.A2b, h2p, 1, n.Wb[2], 1, h2p, n.Y, outp, 0, GemmEpi{n.P + n.off_b[2], nullptr, 0, 0});
-  mark(n);
-  n.last_flop = 2.0 * B * ((double)inp * h1 + (double)h1p * h2 + (double)h2p * out);
+  n.last_flop = 2.0 * B * ((double)inp * h1 + (double)h1p * h2 + (double)h2p * no);
+  return parts;
 }
 
 void loss_grad_impl(hprqp_mlp& n, int B, const float* X, const float* T, const float* w, float* loss_host,
                     float* grad) {
   if (!T) mfail(HPRQP_ERR_ARG, "NULL targets");
-  forward_impl(n, B, X);
-  const int in = n.d[0], h1 = n.d[1], h2 = n.d[2], out = n.d[3];
-  const int inp = n.dp[0], h1p = n.dp[1], h2p = n.dp[2], outp = n.dp[3];
+  MlpOut out;
+  out.T = T; out.w = w;
+  const int parts = forward_impl(n, B, X, out);
+  const int in = n.d[0], h1 = n.d[1], h2 = n.d[2], no = n.d[3];
+  const int h1p = n.dp[1], h2p = n.dp[2], outp = n.dp[3];
   const int Bp = rup8(B);
   const double fwd_flop = n.last_flop;
-  // loss and dY
-  const int gl = eg((long long)B * out);
-  k_standardize<<<gl, 256, 0, n.st>>>(B, out, T, n.out_mean, n.out_istd, n.Tstd);
-  k_mse<<<gl, 256, 0, n.st>>>(B, out, n.Y, outp, n.Tstd, w, n.dYf, n.dYb, outp, n.part);
-  // transposed copies (K = batch for the weight gradients)
-  auto tr = [&](const uint16_t* src, uint16_t* dst, int cols_p) {
-    dim3 g((cols_p + 31) / 32, (Bp + 31) / 32);
-    k_transpose_bf16<<<g, 256, 0, n.st>>>(B, Bp, cols_p, src, dst);
+  float* const G = n.G;
+  // a weight gradient (K = batch) into G and the caller's copy
+  auto wgrad = [&](int l, int M, int N, const uint16_t* At, const uint16_t* Bt) {
+    MlpJob J = job(n, HM_WGRAD, M, N, Bp, At, Bp, Bt, Bp);
+    J.C = G + n.off_W[l]; J.C2 = grad ? grad + n.off_W[l] : nullptr; J.ld = N;
+    return J;
   };
-  tr(n.Xb, n.Xt, inp);
-  tr(n.A1b, n.A1t, h1p);
-  tr(n.A2b, n.A2t, h2p);
-  tr(n.dYb, n.dYt, outp);
-  float* G = n.G;
+  auto back = [&](MlpJob J, float* dA, const float* Z, float* gf, uint16_t* act, uint16_t* actT, int ld) {
+    J.C = dA; J.Z = const_cast<float*>(Z); J.gf = gf; J.act = act; J.actT = actT; J.ld = ld; J.ldt = Bp;
+    return J;
+  };
+  auto bsum = [&](int l, int N, const float* dZ, int ld) {
+    return colsum(B, N, dZ, ld, G + n.off_b[l], grad ? grad + n.off_b[l] : nullptr);
+  };
   mark(n);
-  // layer 3
-  gemm(n, out, h2, Bp, n.dYt, Bp, 1, n.A2t, 1, Bp, G + n.off_W[2], h2, 0);          // dW3 = dY^T A2
-  k_colsum<<<cs_grid(out), 256, 0, n.st>>>(B, out, n.dYf, outp, G + n.off_b[2]);
-  gemm(n, B, h2, outp, n.dYb, outp, 1, n.Wt[2], 1, outp, n.dA2, h2p, 0);             // dA2 = dY W3
+  MlpLaunch p;
+  // dA2 = dY W3, dZ2 = dA2 GELU'(Z2); dW3 = dY^T A2, db3
+  p.job[0] = back(job(n, HM_BACK, B, h2, outp, n.dYb, outp, n.Wt[2], outp), n.dA2, n.Z2, n.dZ2f, n.dZ2b, n.dZ2t, h2p);
+  p.job[1] = wgrad(2, no, h2, n.dYt, n.A2t);
+  p.cs = bsum(2, no, n.dYf, outp);
+  launch(n, p);
+  // dA1 = dZ2 W2, dZ1 = dA1 GELU'(Z1); dW2 = dZ2^T A1, db2
+  p.job[0] = back(job(n, HM_BACK, B, h1, h2p, n.dZ2b, h2p, n.Wt[1], h2p), n.dA1, n.Z1, n.dZ1f, n.dZ1b, n.dZ1t, h1p);
+  p.job[1] = wgrad(1, h2, h1, n.dZ2t, n.A1t);
+  p.cs = bsum(1, h2, n.dZ2f, h2p);
+  launch(n, p);
+  // dW1 = dZ1^T X, db1
+  p.job[0] = wgrad(0, h1, in, n.dZ1t, n.Xt);
+  p.job[1] = MlpJob{};
+  p.cs = bsum(0, h1, n.dZ1f, h1p);
+  launch(n, p);
   mark(n);
-  k_gelu_bwd<<<eg((long long)B * h2), 256, 0, n.st>>>(B, h2, n.dA2, h2p, n.Z2, h2p, n.dZ2f, n.dZ2b, h2p);
-  tr(n.dZ2b, n.dZ2t, h2p);
-  mark(n);
-  // layer 2
-  gemm(n, h2, h1, Bp, n.dZ2t, Bp, 1, n.A1t, 1, Bp, G + n.off_W[1], h1, 0);          // dW2 = dZ2^T A1
-  k_colsum<<<cs_grid(h2), 256, 0, n.st>>>(B, h2, n.dZ2f, h2p, G + n.off_b[1]);
-  gemm(n, B, h1, h2p, n.dZ2b, h2p, 1, n.Wt[1], 1, h2p, n.dA1, h1p, 0);              // dA1 = dZ2 W2
-  mark(n);
-  k_gelu_bwd<<<eg((long long)B * h1), 256, 0, n.st>>>(B, h1, n.dA1, h1p, n.Z1, h1p, n.dZ1f, n.dZ1b, h1p);
-  tr(n.dZ1b, n.dZ1t, h1p);
-  mark(n);
-  // layer 1
-  gemm(n, h1, in, Bp, n.dZ1t, Bp, 1, n.Xt, 1, Bp, G + n.off_W[0], in, 0);           // dW1 = dZ1^T X
-  k_colsum<<<cs_grid(h1), 256, 0, n.st>>>(B, h1, n.dZ1f, h1p, G + n.off_b[0]);
-  mark(n);
-  n.last_flop = fwd_flop + 2.0 * ((double)out * h2 * Bp + (double)B * h2 * outp + (double)h2 * h1 * Bp +
+  n.last_flop = fwd_flop + 2.0 * ((double)no * h2 * Bp + (double)B * h2 * outp + (double)h2 * h1 * Bp +
                                   (double)B * h1 * h2p + (double)h1 * in * Bp);
-  if (grad) HMC(hipMemcpyAsync(grad, G, n.np * sizeof(float), hipMemcpyDeviceToDevice, n.st));
-  std::vector<double> part(gl);
-  HMC(hipMemcpyAsync(part.data(), n.part, gl * sizeof(double), hipMemcpyDeviceToHost, n.st));
+  HMC(hipGetLastError());
   HMC(hipStreamSynchronize(n.st));
   double L = 0.0;
-  for (double p : part) L += p;
+  for (int q = 0; q < parts; ++q) L += n.loss_part[q];
   if (loss_host) *loss_host = (float)L;
 }
 
@@ -730,10 +999,8 @@ hprqp_status hprqp_mlp_create(const int32_t dims[4], int32_t max_batch, const fl
 int64_t hprqp_mlp_num_params(const hprqp_mlp* n) { return n ? n->np : 0; }
 
 hprqp_status hprqp_mlp_forward(hprqp_mlp* n, int32_t batch, const float* X, float* Y) {
-  HM_GUARD(if (!n || !Y) mfail(HPRQP_ERR_ARG, "NULL argument"); forward_impl(*n, batch, X);
-           k_destandardize<<<eg((long long)batch * n->d[3]), 256, 0, n->st>>>(batch, n->d[3], n->Y, n->dp[3],
-                                                                             n->out_mean, n->out_sd, Y);
-           HMC(hipStreamSynchronize(n->st)));
+  HM_GUARD(if (!n || !Y) mfail(HPRQP_ERR_ARG, "NULL argument"); MlpOut out; out.user = Y;
+           forward_impl(*n, batch, X, out); HMC(hipGetLastError()); HMC(hipStreamSynchronize(n->st)));
 }
 
 hprqp_status hprqp_mlp_set_scaling(hprqp_mlp* n, const float* in_mean, const float* in_std, const float* out_mean,
@@ -758,11 +1025,11 @@ hprqp_status hprqp_mlp_warm_start(hprqp_mlp* n, int32_t batch, const float* X, i
       if (qn <= 0 || qm < 0 || (qm + 2 * qn != n->d[3] && qm + 2 * qn + 1 != n->d[3]))
         mfail(HPRQP_ERR_SHAPE, "n_out must equal m + 2 n or m + 2 n + 1");
       if (score && qm + 2 * qn + 1 != n->d[3]) mfail(HPRQP_ERR_SHAPE, "score needs n_out = m + 2 n + 1");
-      forward_impl(*n, batch, X);
-      k_destandardize<<<eg((long long)batch * n->d[3]), 256, 0, n->st>>>(batch, n->d[3], n->Y, n->dp[3], n->out_mean,
-                                                                        n->out_sd, n->Yuser);
-      if (batch > 0)
-        k_warm_start<<<batch, 256, 0, n->st>>>(batch, qn, qm, n->d[3], n->Yuser, L, U, y0, w0, x0, bad, score);
+      MlpOut out;
+      out.L = L; out.U = U; out.y0 = y0; out.w0 = w0; out.x0 = x0; out.bad = bad; out.score = score;
+      out.n = qn; out.m = qm;
+      forward_impl(*n, batch, X, out);
+      k_warm_fix<<<batch, 256, 0, n->st>>>(qn, qm, bad, y0, w0, x0);
       HMC(hipGetLastError());
       HMC(hipStreamSynchronize(n->st)));
 }
@@ -844,8 +1111,10 @@ hprqp_status hprqp_mlp_adam(hprqp_mlp* n, float lr, float beta1, float beta2, fl
   HM_GUARD(if (!n) mfail(HPRQP_ERR_ARG, "NULL handle"); n->adam_t += 1;
            const float c1 = 1.0f - std::pow(beta1, (float)n->adam_t);
            const float c2 = 1.0f - std::pow(beta2, (float)n->adam_t);
-           k_adam<<<eg(n->np), 256, 0, n->st>>>(n->np, n->P, n->G, n->Mm, n->Vv, lr, beta1, beta2, eps, c1, c2);
-           refresh_weights(*n));
+           AdamArgs a = adam_args(*n); a.step = 1;
+           a.lr = lr; a.b1 = beta1; a.b2 = beta2; a.eps = eps; a.c1 = c1; a.c2 = c2;
+           const int nb = n->d[1] + n->d[2] + n->d[3];
+           k_adam<<<a.tiles[0] + a.tiles[1] + a.tiles[2] + (nb + 255) / 256, 256, 0, n->st>>>(a));
 }
 
 hprqp_status hprqp_mlp_get_params(hprqp_mlp* n, float* params_host) {
@@ -862,7 +1131,7 @@ hprqp_status hprqp_mlp_set_params(hprqp_mlp* n, const float* params_host) {
 
 hprqp_status hprqp_mlp_gemm_stats(hprqp_mlp* n, double* ms_host, double* flop_host) {
   HM_GUARD(if (!n) mfail(HPRQP_ERR_ARG, "NULL handle"); HMC(hipStreamSynchronize(n->st)); double ms = 0.0;
-           // GEMM intervals: forward (ev0-1, ev2-3, ev4-5); backward (ev6-7 ... ev10-11) if present
+           // GEMM intervals: forward (ev0-1); backward (ev2-3) if present
            for (int i = 0; i + 1 < n->nev; i += 2) {
              float t = 0.f;
              HMC(hipEventElapsedTime(&t, n->ev[i], n->ev[i + 1]));

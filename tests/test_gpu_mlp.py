@@ -141,6 +141,36 @@ def test_backward_stages_entrywise_and_fp64_reference():
         assert rel_f <= 5e-3, (name, rel_f)
 
 
+@pytest.mark.parametrize("dims,batch", [((5, 9, 33, 11), 1), ((31, 32, 33, 65), 31), ((129, 72, 40, 97), 33),
+                                        ((1501, 64, 1100, 40), 7), ((264, 200, 65, 300), 530)])
+def test_stages_at_edges_of_tiles_slabs_and_splits(dims, batch):
+    """Every stage of the network's GEMMs (tests/mlp_bounds.py) below, at and past
+    the 32 x 32 tile, the 64-wide K slab, the ring of slabs and the K splits, and
+    the transposed copies' padding; the gradient copied to the caller is the one
+    Adam uses."""
+    from paper_2507_02470_amd.surrogate import MLP, init_params
+    print(f"mlp stages dims={dims} batch={batch}", flush=True)
+    rng = np.random.default_rng(batch)
+    p = init_params(dims, seed=6)
+    sc = (rng.standard_normal(dims[0]).astype(np.float32), rng.uniform(0.5, 2, dims[0]).astype(np.float32),
+          rng.standard_normal(dims[3]).astype(np.float32), rng.uniform(0.5, 2, dims[3]).astype(np.float32))
+    X = rng.standard_normal((batch, dims[0])).astype(np.float32)
+    T = rng.standard_normal((batch, dims[3])).astype(np.float32)
+    w = rng.uniform(0.5, 1.5, dims[3]).astype(np.float32)
+    net = MLP(dims, batch + 3, p)
+    net.set_scaling(*sc)
+    Y = net.forward(X).cpu().numpy().astype(np.float64)
+    MB.check_forward(net, p, X, dims, *sc, Y)
+    L, g = net.loss_grad(X, T, w)
+    MB.check_backward(net, p, g.cpu().numpy().astype(np.float64), X, T, w, dims, *sc)
+    Yb, Ts = net.intermediate("Y").astype(np.float64), net.intermediate("Ts").astype(np.float64)
+    ref = float((w.astype(np.float64) * (Yb - Ts) ** 2).sum() / (batch * dims[3]))
+    assert abs(L - ref) <= 4 * 2.0 ** -24 * ref      # FP64 sums of FP32 differences, one FP32 result
+    L2, _ = net.loss_grad(X, T, w, want_grad=False)
+    assert L2 == L
+    net.close()
+
+
 def test_adam_step_matches_its_definition():
     """Two Adam steps (Kingma and Ba; bias-corrected moments) on the library's
     own gradients, against the update written out in FP64 with the library's
