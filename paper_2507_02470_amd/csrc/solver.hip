@@ -432,7 +432,7 @@ void launch_csr_xlds(hprqp_handle& h, const Mat& M, const double* x, const Epi& 
   const size_t lds = (size_t)M.cols * sizeof(double);
   static bool attr_set = false;   // one per epilogue type: dynamic LDS above 64 KB must be enabled
   if (!attr_set) {
-    HQC(hipFuncSetAttribute((const void*)k_csr_stream<Epi, true, BS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    HQC(hipFuncSetAttribute((const void*)k_csr_xstream<Epi, BS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(HQ_XLDS_MAX * sizeof(double))));
     attr_set = true;
   }
@@ -442,7 +442,28 @@ void launch_csr_xlds(hprqp_handle& h, const Mat& M, const double* x, const Epi& 
   const int nblk = (M.rows + BS - 1) / BS;
   const int grid = std::max(1, std::min(nblk, std::min(h.ncu * per_cu, HQ_GRID_CAP)));
   check_red_grid(grid, red);
-  k_csr_stream<Epi, true, BS><<<grid, BS, lds, h.st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red, M.cols);
+  k_csr_xstream<Epi, BS><<<grid, BS, lds, h.st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red, M.cols);
+}
+
+template <class Epi>
+void launch_csr_stream(hprqp_handle& h, const Mat& M, const double* x, const Epi& epi, int j, const RedOut& red) {
+  const int shape = stream_shape(M.rows, M.nnz, h.ncu), grid = hq_grid(M.rows, shape / 10);
+  check_red_grid(grid, red);
+#define HQ_STREAM_CASE(RB, E)                                                                                     \
+  case 10 * RB + E:                                                                                               \
+    k_csr_stream<Epi, RB, E><<<grid, HQ_BLOCK, 0, h.st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red);        \
+    break
+  switch (shape) {
+    HQ_STREAM_CASE(32, 2);
+    HQ_STREAM_CASE(64, 2);
+    HQ_STREAM_CASE(64, 4);
+    HQ_STREAM_CASE(128, 4);
+    HQ_STREAM_CASE(128, 8);
+    HQ_STREAM_CASE(256, 2);
+    HQ_STREAM_CASE(256, 8);
+    default: k_csr_stream<Epi, 32, 4><<<grid, HQ_BLOCK, 0, h.st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red);
+  }
+#undef HQ_STREAM_CASE
 }
 
 template <class Epi>
@@ -478,12 +499,12 @@ void launch_csr(hprqp_handle& h, const Mat& M, const double* x, const Epi& epi, 
     }
     return;
   }
-  // stream kernel: HQ_BLOCK rows per block; row-split kernel: HQ_BLOCK / G rows per block
-  const int grid = M.G == 0 ? hq_grid(M.rows, HQ_BLOCK) : hq_grid(M.rows, HQ_BLOCK / M.G);
+  if (M.G == 0) { launch_csr_stream(h, M, x, epi, j, red); return; }
+  // row-split kernel: HQ_BLOCK / G rows per block
+  const int grid = hq_grid(M.rows, HQ_BLOCK / M.G);
   check_red_grid(grid, red);
   hipStream_t st = h.st;
   switch (M.G) {
-    case 0: k_csr_stream<Epi><<<grid, HQ_BLOCK, 0, st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red); break;
     case 1: k_csr<1, Epi><<<grid, HQ_BLOCK, 0, st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red); break;
     case 2: k_csr<2, Epi><<<grid, HQ_BLOCK, 0, st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red); break;
     case 4: k_csr<4, Epi><<<grid, HQ_BLOCK, 0, st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red); break;

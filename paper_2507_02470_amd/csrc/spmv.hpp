@@ -10,6 +10,33 @@
 // in grid-stride order, so a matrix with a few hundred long rows still
 // spreads over hundreds of waves.  No atomics; the summation order depends
 // only on G.
+//
+// Partial sum of one lane, entries k = b, b + G, ... < en of a row, four at a time:
+// the four columns and values, then the four gathers are in flight together,
+// also at the end of a row (clamped to its last entry, the gathered value then
+// replaced by 0), where a remainder loop would wait for each in turn.
+template <int G>
+__device__ __forceinline__ double row_part(const int* __restrict__ col, const double* __restrict__ val,
+                                           const double* xin, int b, int en) {
+  double sum = 0.0;
+  for (int k = b; k < en; k += 4 * G) {
+    int c[4];
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int kk = min(k + u * G, en - 1);
+      c[u] = ld_stream(col + kk);
+      v[u] = ld_stream(val + kk);
+    }
+    double x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = xin[c[u]];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sum += v[u] * (k + u * G < en ? x[u] : 0.0);
+  }
+  return sum;
+}
+
 template <int G, class Epi>
 __global__ __launch_bounds__(HQ_BLOCK) void k_csr(int nrows, const int* __restrict__ rowptr,
                                                   const int* __restrict__ col,
@@ -29,10 +56,11 @@ __global__ __launch_bounds__(HQ_BLOCK) void k_csr(int nrows, const int* __restri
   for (long long r0 = (long long)blockIdx.x * RPB; r0 < nrows; r0 += (long long)gridDim.x * RPB) {
     const long long row = r0 + gi;
     double sum = 0.0;
+    typename EpiOps<Epi>::type ops;
     if (row < nrows) {
       const int b = rowptr[row], en = rowptr[row + 1];
-#pragma unroll 4
-      for (int k = b + gl; k < en; k += G) sum += ld_stream(val + k) * xin[ld_stream(col + k)];
+      if (gl == 0) ops = EpiOps<Epi>::load(e, (int)row);
+      sum = row_part<G>(col, val, xin, b + gl, en);
     }
     if constexpr (G > 64) {
       __shared__ double wpart[HQ_BLOCK / HQ_WAVE];
@@ -49,38 +77,105 @@ __global__ __launch_bounds__(HQ_BLOCK) void k_csr(int nrows, const int* __restri
     } else if constexpr (G > 1) {
       sum = group_sum<G>(sum);
     }
-    if (row < nrows && gl == 0) e((int)row, sum, acc);
+    if (row < nrows && gl == 0) EpiOps<Epi>::run(e, (int)row, sum, acc, ops);
   }
   if (red.active) block_reduce_store<NR, Epi::MAXMASK>(acc, red);
 }
 
-// CSR-stream SpMV for short rows.  A block owns HQ_BLOCK consecutive rows; the
-// nonzeros of those rows (a contiguous range of the CSR arrays) are streamed
-// in chunks of HQ_STREAM_CHUNK with fully coalesced loads, each thread forming
+// CSR-stream SpMV for short rows.  A block of HQ_BLOCK threads owns RB consecutive
+// rows; their nonzeros (a contiguous range of the CSR arrays) are streamed in
+// chunks with fully coalesced loads, each thread forming
 // val[k] * x[col[k]] for k = c0 + tid, c0 + tid + HQ_BLOCK, ... into LDS; then
-// thread t adds up row t's products in CSR order (a fixed summation order)
-// and runs the epilogue for that row.  Loads of the matrix and of the
-// gathered vector are independent of the row structure, which keeps many
-// gathers in flight per wave.
-//
-// XLDS: the whole input vector (ncols entries) is first copied into LDS
-// (dynamic shared memory) and gathered from there: for vectors that fit
-// (up to HQ_XLDS_MAX entries) the gathers then cost no L2 requests.  The grid
-// is persistent (a few blocks per CU), so the copy is made once per block.
-// BS: threads (= rows) per block; the chunk is 2048 products (4096 for
-// 1024-thread blocks, keeping 32 KB of LDS beside the vector's copy).
+// thread t < RB adds up row t's products in CSR order (a fixed summation order)
+// and runs the epilogue for that row.
+// What bounds it: up to a few 1e5 rows, the chain of dependent memory latencies
+// (row pointers, entries, gathers, epilogue operands), so the chain has no more
+// links than these: the block's range comes by scalar loads, every entry of a
+// chunk is in flight at once and then every gather (no load is conditional: the
+// waits between them then count exactly; threads past the end of a chunk repeat
+// its last entry), and the epilogue's operands arrive with the entries.  RB and
+// the E entries a thread takes of a chunk follow the matrix (stream_shape).
 #define HQ_STREAM_CHUNK 2048
+template <class Epi, int RB, int E>
+__global__ __launch_bounds__(HQ_BLOCK) void k_csr_stream(int nrows, const int* __restrict__ rowptr,
+                                                         const int* __restrict__ col,
+                                                         const double* __restrict__ val,
+                                                         const double* __restrict__ xin, Epi epi,
+                                                         const DevParams* __restrict__ prm, int j, RedOut red) {
+  constexpr int NR = Epi::NR;
+  constexpr int CH = E * HQ_BLOCK;
+  __shared__ double prod[CH];
+  Epi e = epi;
+  e.setup(prm, j);
+  double acc[NR > 0 ? NR : 1];
+#pragma unroll
+  for (int s = 0; s < (NR > 0 ? NR : 1); ++s) acc[s] = 0.0;
+  const int t = threadIdx.x;
+  const int nblk = (nrows + RB - 1) / RB;
+  for (int rb = blockIdx.x; rb < nblk; rb += gridDim.x) {
+    const int r0 = rb * RB, nr = min(RB, nrows - r0);
+    const int kb = rowptr[r0], ke = rowptr[r0 + nr];
+    const int tr = min(t, nr - 1);   // (threads past the rows repeat the last row's loads)
+    const int myb = rowptr[r0 + tr], mye = t < nr ? rowptr[r0 + tr + 1] : 0;
+    const typename EpiOps<Epi>::type ops = EpiOps<Epi>::load(e, r0 + tr);
+    double sum = 0.0;
+    for (int c0 = kb; c0 < ke; c0 += CH) {
+      const int c1 = min(ke, c0 + CH);
+      int ci[E];
+      double v[E], x[E];
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const int k = min(c0 + t + u * HQ_BLOCK, c1 - 1);
+        ci[u] = ld_stream(col + k);
+        v[u] = ld_stream(val + k);
+      }
+#pragma unroll
+      for (int u = 0; u < E; ++u) x[u] = xin[ci[u]];
+#pragma unroll
+      for (int u = 0; u < E; ++u) prod[t + u * HQ_BLOCK] = v[u] * x[u];   // (past the end: never read)
+      __syncthreads();
+      const int lo = max(myb, c0), hi = min(mye, c1);
+      for (int k = lo; k < hi; k += 4) {
+        double q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = prod[min(k + u, hi - 1) - c0];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (k + u < hi) sum += q[u];
+      }
+      __syncthreads();
+    }
+    if (t < nr) EpiOps<Epi>::run(e, r0 + t, sum, acc, ops);
+  }
+  if (red.active) block_reduce_store<NR, Epi::MAXMASK>(acc, red);
+}
+
+// Shape of k_csr_stream, as 10 RB + E: the most rows per block that still give every
+// CU a block and whose entries mostly fit one chunk, then the smallest chunk that
+// holds them (random rows of 5 and 10 entries, n = 2e4, m = 1e4: 4.7 us a product
+// with 32 rows, 4.4 and 6.9 with 256; larger chunks than needed cost their loads)
+inline int stream_shape(int rows, long long nnz, int ncu) {
+  const double avg = rows > 0 ? (double)nnz / rows : 0.0;
+  const int shapes[][2] = {{256, 2}, {256, 8}, {128, 4}, {128, 8}, {64, 2}, {64, 4}, {32, 2}};
+  for (const auto& s : shapes)
+    if ((long long)rows >= (long long)ncu * s[0] && 1.05 * avg * s[0] <= HQ_BLOCK * s[1]) return 10 * s[0] + s[1];
+  return 1.05 * avg * 32 <= 2 * HQ_BLOCK ? 322 : 324;
+}
+
+// The stream kernel gathering from a copy of the whole input vector in LDS
+// (dynamic shared memory, ncols <= HQ_XLDS_MAX entries): the gathers then cost no
+// L2 requests.  Persistent blocks of BS threads (= rows per pass), so the copy is
+// made once per block; chunks of 4096 products (32 KB of LDS beside the copy).
 #define HQ_XLDS_MAX 14336
 #define HQ_XLDS_BLOCK 1024
-template <class Epi, bool XLDS = false, int BS = HQ_BLOCK>
-__global__ __launch_bounds__(BS) void k_csr_stream(int nrows, const int* __restrict__ rowptr,
-                                                   const int* __restrict__ col,
-                                                   const double* __restrict__ val,
-                                                   const double* __restrict__ xin, Epi epi,
-                                                   const DevParams* __restrict__ prm, int j, RedOut red,
-                                                   int ncols = 0) {
+template <class Epi, int BS>
+__global__ __launch_bounds__(BS) void k_csr_xstream(int nrows, const int* __restrict__ rowptr,
+                                                    const int* __restrict__ col,
+                                                    const double* __restrict__ val,
+                                                    const double* __restrict__ xin, Epi epi,
+                                                    const DevParams* __restrict__ prm, int j, RedOut red, int ncols) {
   constexpr int NR = Epi::NR;
-  constexpr int CH = BS > HQ_BLOCK ? 2 * HQ_STREAM_CHUNK : HQ_STREAM_CHUNK;
+  constexpr int CH = 2 * HQ_STREAM_CHUNK;
   __shared__ double prod[CH];
   __shared__ int srp[BS + 1];
   extern __shared__ double xs[];
@@ -90,11 +185,8 @@ __global__ __launch_bounds__(BS) void k_csr_stream(int nrows, const int* __restr
 #pragma unroll
   for (int s = 0; s < (NR > 0 ? NR : 1); ++s) acc[s] = 0.0;
   const int t = threadIdx.x;
-  if constexpr (XLDS) {
-    for (int i = t; i < ncols; i += BS) xs[i] = xin[i];
-    __syncthreads();
-  }
-  const double* xg = XLDS ? xs : xin;
+  for (int i = t; i < ncols; i += BS) xs[i] = xin[i];
+  __syncthreads();
   const int nblk = (nrows + BS - 1) / BS;
   for (int rb = blockIdx.x; rb < nblk; rb += gridDim.x) {
     const int r0 = rb * BS;
@@ -107,7 +199,7 @@ __global__ __launch_bounds__(BS) void k_csr_stream(int nrows, const int* __restr
     for (int c0 = kb; c0 < ke; c0 += CH) {
       const int c1 = min(ke, c0 + CH);
 #pragma unroll 4
-      for (int k = c0 + t; k < c1; k += BS) prod[k - c0] = ld_stream(val + k) * xg[ld_stream(col + k)];
+      for (int k = c0 + t; k < c1; k += BS) prod[k - c0] = ld_stream(val + k) * xs[ld_stream(col + k)];
       __syncthreads();
       const int lo = max(myb, c0), hi = min(mye, c1);
       for (int k = lo; k < hi; ++k) sum += prod[k - c0];

@@ -432,3 +432,39 @@ def test_max_iter_and_warm_start():
     r3 = s2.solve(y0=r2.y, w0=r2.w, x0=r2.x)
     assert r3.term == "solved" and r3.iters <= r2.iters // 2
     s.close(); s2.close()
+
+
+@pytest.mark.parametrize("lanes", [0, 4, 64])
+@pytest.mark.parametrize("rows,avg", [(1, 3), (31, 16), (33, 40), (8191, 5), (8193, 17), (16385, 8), (32769, 10),
+                                      (65535, 2), (65537, 7), (70000, 1)])
+def test_row_products_at_edges_of_blocks_and_chunks(rows, avg, lanes):
+    """The CSR-stream kernel over its shapes (rows per block 32 to 256, 2 to 8 entries
+    a thread), and the row-split kernel: empty rows, rows longer than a chunk, a
+    ragged last block, one infinite and one NaN entry of the vector.  Bound: a
+    sum of k products is off by at most (k + 1) u times their absolute sum."""
+    import scipy.sparse as sp
+    DP, Solver = _S()
+    rng = np.random.default_rng(rows + avg)
+    cols = 5000
+    lens = rng.poisson(avg, rows)
+    lens[rng.random(rows) < 0.1] = 0
+    lens[rows // 2] = 3000
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    ci = rng.integers(0, cols - 2, rp[-1])
+    ci[rng.random(rp[-1]) < 2.0 / rp[-1]] = cols - 1
+    ci[-1] = cols - 2
+    v = rng.standard_normal(rp[-1])
+    print(f"row products rows={rows} avg={avg} lanes={lanes}", flush=True)
+    qp = qpgen.QP(n=cols, m=rows, qkind="zero", c=np.ones(cols), L=np.zeros(cols), U=np.ones(cols), a_rowptr=rp,
+                  a_col=ci, a_val=v, l=np.zeros(rows), u=np.ones(rows))
+    s = Solver(DP(qp), lambda_A=1.0, tol=0.0, max_iter=1, spmv_lanes=lanes)
+    # (|A| by entry: abs() of a matrix would first add up repeated columns)
+    A, absA = (sp.csr_matrix((w, ci.copy(), rp.copy()), shape=(rows, cols)) for w in (v.copy(), np.abs(v)))
+    x = rng.standard_normal(cols)
+    got = s.apply("A", x).cpu().numpy()
+    bound = (lens + 1) * 2.0 ** -53 * (absA @ np.abs(x)) * 2.0        # both sides round
+    assert np.all(np.abs(got - A @ x) <= bound)
+    x[cols - 2], x[cols - 1] = np.inf, np.nan
+    got, want = s.apply("A", x).cpu().numpy(), A @ x
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    s.close()
