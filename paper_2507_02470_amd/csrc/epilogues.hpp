@@ -261,13 +261,18 @@ struct EpiStore2 {
   __device__ __forceinline__ void operator()(int i, double q, double*) const { a[i] = q; b[i] = q; }
 };
 
-// power method: w = M v stored; acc[0] += v_i w_i (Rayleigh quotient), acc[1] += w_i^2
+// power method: w = s M v stored; acc[0] += v_i w_i (Rayleigh quotient), acc[1] += w_i^2
 struct EpiPow {
   const double* v; double* w;
+  double s;
   static constexpr int NR = 2;
   static constexpr unsigned MAXMASK = 0u;
   __device__ void setup(const DevParams*, int) {}
-  __device__ __forceinline__ void operator()(int i, double q, double* acc) const {
-    w[i] = q; acc[0] += v[i] * q; acc[1] += q * q;
+  struct Ops { double v; };
+  __device__ __forceinline__ Ops load(int i) const { return Ops{v[i]}; }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc, const Ops& o) const {
+    const double wi = q * s;
+    w[i] = wi; acc[0] += o.v * wi; acc[1] += wi * wi;
   }
 };

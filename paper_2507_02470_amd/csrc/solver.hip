@@ -71,11 +71,10 @@ enum : int {
   SL_RA = 19,   // primal residual part: 4 slots
   SL_RQ = 23,   // dual residual part: 7 slots
   SL_ITER_END = 30,
-  SL_POW = 30,  // power method: 2 slots
-  SL_NRM = 32,  // norms of b and c: 4 slots
-  SL_LR = 36,   // F^T x of the low-rank Q: 16 slots
-  SL_QWX = 52,  // ||Q(w - x)||_inf at the returned point: 1 slot
-  SL_TOTAL = 53
+  SL_NRM = 30,  // norms of b and c: 4 slots
+  SL_LR = 34,   // F^T x of the low-rank Q: 16 slots
+  SL_QWX = 50,  // ||Q(w - x)||_inf at the returned point: 1 slot
+  SL_TOTAL = 51
 };
 static constexpr unsigned long long kMaxMask =
     (1ull << (SL_RA + 0)) | (1ull << (SL_RA + 1)) | (1ull << (SL_RQ + 0)) | (1ull << (SL_RQ + 1)) |
@@ -135,28 +134,7 @@ __global__ void k_copy(long long n, const double* __restrict__ s, double* __rest
     if (b) b[i] = v;
   }
 }
-// power method: reduce slots (<v,w>, |w|^2) into the history and the next scale
-__global__ __launch_bounds__(256) void k_pow_final(const double* __restrict__ partials, const int* __restrict__ counts,
-                                                   double* __restrict__ hist, int it, double* __restrict__ scale) {
-  __shared__ double sh[2][4];
-  for (int s = 0; s < 2; ++s) {
-    const int slot = SL_POW + s, cnt = counts[slot];
-    double v = 0.0;
-    for (int i = threadIdx.x; i < cnt; i += blockDim.x) v += partials[(size_t)slot * HQ_PCAP + i];
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) sh[s][threadIdx.x >> 6] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double lam = sh[0][0], nw2 = sh[1][0];
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) { lam += sh[0][w]; nw2 += sh[1][w]; }
-    hist[2 * it] = lam;
-    hist[2 * it + 1] = nw2;
-    *scale = nw2 > 0.0 ? 1.0 / sqrt(nw2) : 0.0;
-  }
-}
-__global__ void k_scale(long long n, const double* __restrict__ in, const double* __restrict__ s, double* __restrict__ out) {
-  const double f = *s;
+__global__ void k_scale(long long n, const double* __restrict__ in, double f, double* __restrict__ out) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
     out[i] = in[i] * f;
 }
@@ -291,7 +269,7 @@ struct hprqp_handle {
   // iterations (m each); t, its anchor and bar, dt (n each)
   double *pe = nullptr, *pax = nullptr, *pdy = nullptr, *pt = nullptr, *pta = nullptr, *ptb = nullptr,
          *pdt = nullptr;
-  double *partials = nullptr, *scalars = nullptr, *hist = nullptr;
+  double *partials = nullptr, *scalars = nullptr;
   int* counts = nullptr;
   int* dflags = nullptr;
   DevParams* dprm = nullptr;
@@ -885,49 +863,71 @@ double golden_sigma(double th1, double th2, double th3, double lamQ) {
 // Power method on A A^T (which = 0, vectors of length m) or Q (which = 1, length n):
 // v <- start/|start|; repeat w = M v, lambda = <v, w>, v <- w/|w|; stop at the first
 // iteration whose Rayleigh quotient changes by <= tol relative (Section 4.1).
+// An iteration is the products alone: w = s M v is kept unnormalized, with s fixed for
+// a chunk of iterations (the reciprocal growth at its start, so that the size of
+// w hardly changes), each iteration's <v, w> and |w|^2 go to reduction slots of
+// their own (those of the solve, unused at setup), and the quotients
+// <v, w> / (s |v|^2) are formed on the host when the chunk is done.  Normalizing
+// in every iteration took two more launches of 2.5 us behind products of 8.
+// A chunk that overflows or underflows (growth of more than 1e9 past its start's
+// estimate) is taken again from its start vector one iteration at a time.
 double power_method(hprqp_handle& h, int which, const double* start, int maxit, double tol, int* iters_out) {
   const long long k = which == 0 ? h.m : h.n;
   if (k == 0) { if (iters_out) *iters_out = 0; return 0.0; }
-  double* v = h.t1;   // current unit vector
-  double* wv = h.t2;  // product
-  double* tmpn = h.kronT ? nullptr : nullptr;
-  (void)tmpn;
-  double* mid = (which == 0) ? h.xh : nullptr;  // A^T v (n) for the A A^T case; xh is free at setup
-  if (start) k_copy<<<hq_grid(k, 256), 256, 0, h.st>>>(k, start, v, nullptr);
-  else k_fill<<<hq_grid(k, 256), 256, 0, h.st>>>(k, v, 1.0);
-  launch_elem(h, (int)k, nullptr, EpiSumSq{v}, 0, red_seq(h, SL_POW, 1));
-  final_reduce(h, SL_POW, 1);
-  HQC(hipMemcpyAsync(h.hs, h.scalars + SL_POW, sizeof(double), hipMemcpyDeviceToHost, h.st));
-  HQC(hipStreamSynchronize(h.st));
-  const double s0 = h.hs[0] > 0.0 ? 1.0 / std::sqrt(h.hs[0]) : 0.0;
-  h.hs[1] = s0;
-  HQC(hipMemcpyAsync(h.scalars + SL_TOTAL, h.hs + 1, sizeof(double), hipMemcpyHostToDevice, h.st));
-  k_scale<<<hq_grid(k, 256), 256, 0, h.st>>>(k, v, h.scalars + SL_TOTAL, v);
-  const int chunk = 16;
-  std::vector<double> hist;
-  double lam = 0.0;
-  int stop_it = -1;
-  for (int it0 = 1; it0 <= maxit && stop_it < 0; it0 += chunk) {
-    const int it1 = std::min(maxit, it0 + chunk - 1);
-    for (int it = it0; it <= it1; ++it) {
-      if (which == 0) {
-        launch_csr(h, h.AT, v, EpiStore{mid}, 0, no_red(h));
-        launch_csr(h, h.A, mid, EpiPow{v, wv}, 0, red_seq(h, SL_POW, 2));
-      } else {
-        q_apply(h, v, EpiPow{v, wv}, 0, red_seq(h, SL_POW, 2));
-      }
-      k_pow_final<<<1, 256, 0, h.st>>>(h.partials, h.counts, h.hist, it, h.scalars + SL_TOTAL);
-      k_scale<<<hq_grid(k, 256), 256, 0, h.st>>>(k, wv, h.scalars + SL_TOTAL, v);
-    }
-    std::vector<double> hh(2 * (it1 + 1));
-    HQC(hipMemcpyAsync(hh.data(), h.hist, hh.size() * sizeof(double), hipMemcpyDeviceToHost, h.st));
+  constexpr int CHUNK = SL_ITER_END / 2;                     // iterations per chunk: 2 slots each, all sums
+  auto reduce_to_host = [&](int slots) {
+    k_final_reduce<<<slots, 256, 0, h.st>>>(h.partials, h.counts, 0, 0ull, h.scalars);
+    HQC(hipMemcpyAsync(h.hs, h.scalars, slots * sizeof(double), hipMemcpyDeviceToHost, h.st));
     HQC(hipStreamSynchronize(h.st));
-    for (int it = it0; it <= it1; ++it) {
-      lam = hh[2 * it];
-      const double nw2 = hh[2 * it + 1];
-      if (nw2 == 0.0) { stop_it = it; break; }
-      if (it > 1 && std::fabs(lam - hh[2 * (it - 1)]) <= tol * std::fabs(lam)) { stop_it = it; break; }
+  };
+  double* const base = which == 0 ? h.ya : h.g;              // a chunk's start, |base|^2 = 1 up to rounding
+  double* const buf[2] = {which == 0 ? h.ybar : h.t1, which == 0 ? h.tm : h.t2};
+  if (start) k_copy<<<hq_grid(k, 256), 256, 0, h.st>>>(k, start, buf[0], nullptr);
+  else k_fill<<<hq_grid(k, 256), 256, 0, h.st>>>(k, buf[0], 1.0);
+  launch_elem(h, (int)k, nullptr, EpiSumSq{buf[0]}, 0, red_seq(h, 0, 1));
+  reduce_to_host(1);
+  double norm2 = h.hs[0];                                     // |cur|^2, cur the last vector
+  const double* cur = buf[0];
+  double lam = 0.0, prev = 0.0, growth = 0.0;
+  int it = 0, stop_it = -1, len = 1;
+  while (it < maxit && stop_it < 0) {
+    k_scale<<<hq_grid(k, 256), 256, 0, h.st>>>(k, cur, norm2 > 0.0 ? 1.0 / std::sqrt(norm2) : 0.0, base);
+    const bool first = growth == 0.0;                         // the first iteration finds the growth
+    int L = first ? 1 : std::min(std::min(len, CHUNK), maxit - it);
+    const double s = first ? 1.0 : 1.0 / growth;
+    for (;;) {
+      const double* v = base;
+      for (int q = 0; q < L; ++q) {
+        double* const w = buf[q & 1];
+        const EpiPow epi{v, w, s};
+        if (which == 0) {
+          launch_csr(h, h.AT, v, EpiStore{h.xh}, 0, no_red(h));   // (xh is free at setup)
+          launch_csr(h, h.A, h.xh, epi, 0, red_seq(h, 2 * q, 2));
+        } else {
+          q_apply(h, v, epi, 0, red_seq(h, 2 * q, 2));
+        }
+        v = w;
+      }
+      cur = v;
+      reduce_to_host(2 * L);
+      bool fine = true;
+      for (int q = 0; q < 2 * L; ++q) fine &= std::isfinite(h.hs[q]);
+      for (int q = 0; q < L; ++q) fine &= h.hs[2 * q + 1] >= 1e-280;
+      if (fine || L == 1) break;
+      L = 1;                                                  // again, one iteration from the same start
     }
+    double vv = 1.0;                                          // |v|^2 of the iteration
+    for (int q = 0; q < L && stop_it < 0; ++q) {
+      ++it;
+      lam = h.hs[2 * q] / (s * vv);
+      norm2 = h.hs[2 * q + 1];
+      if (!std::isfinite(lam)) { it = maxit; break; }
+      if (norm2 == 0.0 || (it > 1 && std::fabs(lam - prev) <= tol * std::fabs(lam))) stop_it = it;
+      prev = lam;
+      if (norm2 > 0.0) growth = std::sqrt(norm2 / vv) / s;
+      vv = norm2;
+    }
+    len = first || L > 1 || len == 1 ? CHUNK : 1;             // after a failed chunk: one by one, then chunks again
   }
   if (iters_out) *iters_out = stop_it < 0 ? maxit : stop_it;
   return lam;
@@ -1232,7 +1232,6 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
     h.partials = h.dalloc<double>((size_t)SL_TOTAL * HQ_PCAP);
     h.counts = h.dalloc<int>(SL_TOTAL);
     h.scalars = h.dalloc<double>(SL_TOTAL + 8);
-    h.hist = h.dalloc<double>(2 * 5002);
     h.dflags = h.dalloc<int>(1);
     h.dprm = h.dalloc<DevParams>(1);
     HQC(hipHostMalloc((void**)&h.hs, 64 * sizeof(double), hipHostMallocDefault));

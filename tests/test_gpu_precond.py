@@ -148,3 +148,39 @@ def test_matrix_free_q_ignores_preconditioning():
     assert r0.iters == r1.iters
     assert torch.equal(r0.x, r1.x)
     s0.close(); s1.close()
+
+
+@pytest.mark.parametrize("scale,start", [(1.0, "ones"), (1e60, "ones"), (1e-60, "ones"), (1e10, "hidden"), (1e25, "hidden")])
+def test_power_method_over_scales_and_starts(scale, start):
+    """The power method keeps its vector unnormalized over a chunk of iterations:
+    matrices of extreme scale, and a start almost orthogonal to the dominant
+    direction (the chunk overflows and is taken again step by step), give the
+    estimate and count of the method as stated, written out here.  A diagonal A
+    makes every step exact up to roundings: 3 u a step and entry, n u a sum."""
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    n = 64
+    rng = np.random.default_rng(9)
+    a = np.sqrt(scale) * rng.uniform(0.5, 1.0, n)
+    v0 = np.ones(n)
+    if start == "hidden":
+        a[:] = rng.uniform(0.5, 1.0, n)
+        a[5] = scale
+        v0[5] = 1e-3 / scale ** 2
+    rows = np.arange(n + 1)
+    qp = qpgen.QP(n=n, m=n, qkind="zero", c=np.ones(n), L=np.zeros(n), U=np.ones(n), a_rowptr=rows,
+                  a_col=np.arange(n), a_val=a, l=np.zeros(n), u=np.ones(n))
+    print(f"power method scale={scale} start={start}", flush=True)
+    s = Solver(DeviceProblem(qp), power_start_A=v0, tol=0.0, max_iter=1)
+    info = s.power_info()
+    s.close()
+    v = v0 / np.linalg.norm(v0)
+    lam = 0.0
+    for it in range(1, 5001):
+        w = a * (a * v)
+        new = v @ w
+        stop = it > 1 and abs(new - lam) <= 1e-6 * abs(new)
+        lam, v = new, w / np.linalg.norm(w)
+        if stop:
+            break
+    assert info["it_A"] == it
+    assert abs(info["est_A"] - lam) <= 2 * (6 * it + 2 * n + 10) * 2.0 ** -53 * lam
