@@ -164,6 +164,28 @@ struct EpiQ2 {
   }
 };
 
+// Without rows (m = 0) d = 0 and Q d = 0, so the Q xhat product carries the whole
+// iteration: wbar = w_half and EpiQ2 directly on q1 = Q xhat.  For products whose
+// last step gathers neither xh nor any other vector written here (the Gram Q: it
+// gathers Ahat xhat).
+struct EpiQ0 {
+  EpiQ2 e;
+  static constexpr int NR = EpiQ2::NR;
+  static constexpr unsigned MAXMASK = EpiQ2::MAXMASK;
+  __device__ void setup(const DevParams* p, int j) { e.setup(p, j); }
+  using Ops = EpiQ2::Ops;
+  __device__ __forceinline__ Ops load(int i) const {
+    return Ops{ld_stream(e.xh + i), ld_stream(e.w + i), ld_stream(e.Qw + i), 0.0, 0.0, ld_stream(e.wa + i),
+               ld_stream(e.Qwa + i), ld_stream(e.xa + i), ld_stream(e.ATy + i), ld_stream(e.c + i), ld_stream(e.L + i),
+               ld_stream(e.U + i)};
+  }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
+  __device__ __forceinline__ void operator()(int i, double q, double* acc, Ops o) const {
+    o.q1 = q;
+    e(i, 0.0, acc, o);
+  }
+};
+
 // Stand-alone z/x step (start of a solve and after a restart):
 //   r_z = x + sigma(-Qw + A^T y - c); xbar = Pi_C(r_z); zbar = (xbar - r_z)/sigma; xh = 2 xbar - x.
 struct EpiStage1 {

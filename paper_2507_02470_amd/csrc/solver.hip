@@ -218,6 +218,7 @@ struct Mat {
   PanelMat pm;        // panel-ordered copy (pm.pp == nullptr: not built)
   int G_np = 0;       // kernel used in place of the panel-ordered one under a heavy epilogue
   SplitMat sm;        // column-split copy (sm.off == nullptr: not built)
+  const unsigned short* c16 = nullptr;   // 16-bit columns (nullptr: not built)
 };
 
 #define HQ_PROF_ITERS 64
@@ -384,15 +385,15 @@ void launch_xrow_g(hprqp_handle& h, const Mat& M, const double* x, const Epi& ep
   // persistent grid: as many blocks as fit on the CUs at this LDS size
   const size_t per_block = lds + 16 * 16 * sizeof(double) + 2048;
   const int per_cu = std::max(1, (int)((160 * 1024) / per_block));
-  const long long groups = ((long long)M.rows + BS / G - 1) / (BS / G);
-  const int grid = (int)std::max(1ll, std::min(groups, (long long)std::min(h.ncu * per_cu, HQ_GRID_CAP)));
+  const long long passes = ((long long)M.rows + BS - 1) / BS;   // 64 rows per wave
+  const int grid = (int)std::max(1ll, std::min(passes, (long long)std::min(h.ncu * per_cu, HQ_GRID_CAP)));
   check_red_grid(grid, red);
-  k_csr_xrow<G, Epi><<<grid, BS, lds, h.st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red, M.cols);
+  k_csr_xrow<G, Epi><<<grid, BS, lds, h.st>>>(M.rows, M.rp, M.c16, M.v, x, epi, h.dprm, j, red, M.cols);
 }
 
 template <class Epi>
 void launch_csr_xrow(hprqp_handle& h, const Mat& M, const double* x, const Epi& epi, int j, const RedOut& red) {
-  if (M.cols > HQ_XLDS_MAX) fail(HPRQP_ERR_UNSUPPORTED, "LDS-gather kernel: vector too long");
+  if (M.cols > HQ_XLDS_MAX || (M.nnz > 0 && !M.c16)) fail(HPRQP_ERR_UNSUPPORTED, "LDS-gather kernel: vector too long");
   switch (HQ_G_XROW - M.G) {
     case 1: launch_xrow_g<1>(h, M, x, epi, j, red); break;
     case 2: launch_xrow_g<2>(h, M, x, epi, j, red); break;
@@ -657,10 +658,14 @@ void enqueue_iter(hprqp_handle& h, int j, int Tseg, bool trace, bool prof) {
   auto mark = [&](int kind, int edge) {
     if (ps >= 0) HQC(hipEventRecord(h.pev[ps][kind][edge], h.st));
   };
+  // without rows the Gram Q's product carries the whole iteration (EpiQ0)
+  const bool one = h.m == 0 && h.qkind == HPRQP_Q_GRAM;
   // a3: q1 = Q xhat, v
-  mark(0, 0);
-  q_apply(h, h.xh, EpiQ1{h.xh, h.Qw, h.v, h.q1, 0.0}, j, no_red(h));
-  mark(0, 1);
+  if (!one) {
+    mark(0, 0);
+    q_apply(h, h.xh, EpiQ1{h.xh, h.Qw, h.v, h.q1, 0.0}, j, no_red(h));
+    mark(0, 1);
+  }
   if (h.m > 0) {
     // a4: A v, ybar, y+
     RedOut r4 = no_red(h);
@@ -695,9 +700,12 @@ void enqueue_iter(hprqp_handle& h, int j, int Tseg, bool trace, bool prof) {
   if (check)
     for (int s = 0; s < 3; ++s) r6.slot[6 + s] = (int8_t)(SL_TH + 1 + s);
   r6.active = want_r || check;
-  mark(3, 0);
-  if (h.m > 0) q_apply(h, h.d, e6, j, r6, true);
+  if (one) mark(0, 0);
+  else mark(3, 0);
+  if (one) q_apply(h, h.xh, EpiQ0{e6}, j, r6);
+  else if (h.m > 0) q_apply(h, h.d, e6, j, r6, true);
   else launch_elem(h, h.n, nullptr, e6, j, r6);  // Q A^T(ybar - y) = 0 without constraints
+  if (one) mark(0, 1), mark(3, 0);   // (nothing is left for the fourth product)
   mark(3, 1);
   if (check && h.m > 0 && h.qkind != HPRQP_Q_ZERO)
     q_apply(h, h.e, EpiTheta3{h.e}, j, red_seq(h, SL_TH + 4, 1));
@@ -933,6 +941,14 @@ double power_method(hprqp_handle& h, int which, const double* start, int maxit, 
   return lam;
 }
 
+// 16-bit columns of M for the row-split kernel gathering from LDS
+void build_c16(hprqp_handle& h, Mat& M) {
+  if (M.c16 || M.rows == 0 || M.nnz == 0 || M.cols > HQ_XLDS_MAX) return;
+  unsigned short* c = h.dalloc<unsigned short>((size_t)M.nnz);
+  k_cols16<<<hq_grid(M.nnz, 256), 256, 0, h.st>>>(M.nnz, M.ci, c);
+  M.c16 = c;
+}
+
 // Panel-ordered copy of M (panel.hpp); false when a chunk would need more than
 // 16-bit local offsets or the matrix is too small to gain from it
 bool build_panel(hprqp_handle& h, Mat& M, bool any_size = false) {
@@ -1050,6 +1066,7 @@ void autotune_csr(hprqp_handle& h, Mat& M, const double* x, double* out) {
     if (lanes > 1 && M.maxlen >= 0 && M.maxlen <= 4096 && (double)lanes > 4.0 * ((double)M.nnz / M.rows) &&
         lanes > 8)
       continue;
+    if (is_xrow(G)) build_c16(h, M);
     M.G = G;
     launch_csr(h, M, x, EpiStore{out}, 0, no_red(h));
     // one timed launch first: a candidate already twice as slow as the best
@@ -1350,14 +1367,15 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
       M.maxlen = mx;
       if (M.G > 0 && M.cols <= HQ_XLDS_MAX && M.rows >= 65536) {
         // many long rows over a vector that fits LDS: the row-split kernel
-        // gathering from LDS, about six nonzeros per lane (the Lasso's
-        // Ahat^T, 100 per row: 173 us with 16 lanes against 350 us through
-        // the L2 and 250 us with 64 lanes from LDS)
+        // gathering from LDS, with lanes for up to seven entries each (the
+        // Lasso's Ahat^T, 100 per row: 16 lanes; through the L2 it takes three
+        // times as long)
         const double avg = (double)M.nnz / M.rows;
         int g = 1;
-        while (g < HQ_WAVE && 6.0 * 2 * g <= avg) g *= 2;
+        while (g < HQ_WAVE && 7.0 * g < avg) g *= 2;
         M.G = HQ_G_XROW - g;
         M.G_np = M.G;
+        build_c16(h, M);
       } else if (M.G > 0 && (long long)M.cols * 8 > (3ll << 20) && build_split(h, M)) {
         // long rows over a vector larger than three quarters of an XCD's L2:
         // the column-split product (the Lasso's Ahat, 1e4 rows of 5000 over a
@@ -1447,6 +1465,7 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
         // the LDS copy needs a small vector: the row-split kernel with g lanes otherwise
         M->G = M->cols > HQ_XLDS_MAX ? g : opt->spmv_lanes;
         M->G_np = M->G;
+        if (is_xrow(M->G)) build_c16(h, *M);
       }
     } else if (opt->spmv_lanes != -1) {
       fail(HPRQP_ERR_ARG, "spmv_lanes must be -4, -3, -2, -1, 0, a power of 2 <= 256 or -100 - g (g <= 64)");
@@ -1459,6 +1478,7 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
       if (!h.pre) { M0 = M; return; }
       const auto layout = [](int G) { return G == HQ_G_PANEL || G == HQ_G_SPLIT; };
       M0.maxlen = M.maxlen;
+      M0.c16 = M.c16;   // the same columns
       M0.G = layout(M.G) ? (layout(M.G_np) ? 0 : M.G_np) : M.G;
       M0.G_np = M0.G;
     };

@@ -143,3 +143,29 @@ def test_batch_rejects_l1():
     qp.l1_weight = 0.1
     with pytest.raises(HPRQPError):
         BatchSolver([qp], tol=1e-8, max_iter=1000)
+
+
+@pytest.mark.parametrize("rows,cols,avg,g", [(3, 40, 9, 1), (64, 300, 20, 2), (65, 300, 30, 8), (1000, 14336, 130, 16),
+                                             (20_001, 700, 25, 4), (200, 9000, 700, 64), (66_000, 500, 40, 0)])
+def test_row_split_products_from_lds(rows, cols, avg, g):
+    """The row-split kernel over an LDS copy of the vector (16-bit columns, 64 rows a
+    wave): every lane count, empty rows, rows past the eight entries a lane has in
+    flight, a ragged last wave; g = 0 takes the default choice.  Bound: a sum of k
+    products is off by at most (k + 1) u times their absolute sum."""
+    import scipy.sparse as sp
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    rng = np.random.default_rng(rows)
+    lens = rng.poisson(avg, rows)
+    lens[rng.random(rows) < 0.1] = 0
+    lens[rows // 3] = 10 * avg
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    ci, v = rng.integers(0, cols, rp[-1]), rng.standard_normal(rp[-1])
+    print(f"lds rows={rows} cols={cols} avg={avg} g={g}", flush=True)
+    qp = qpgen.QP(n=cols, m=rows, qkind="zero", c=np.ones(cols), L=np.zeros(cols), U=np.ones(cols), a_rowptr=rp,
+                  a_col=ci, a_val=v, l=np.zeros(rows), u=np.ones(rows))
+    s = Solver(DeviceProblem(qp), lambda_A=1.0, tol=0.0, max_iter=1, spmv_lanes=-100 - g if g else -1)
+    A, absA = (sp.csr_matrix((w, ci.copy(), rp.copy()), shape=(rows, cols)) for w in (v.copy(), np.abs(v)))
+    x = rng.standard_normal(cols)
+    got = s.apply("A", x).cpu().numpy()
+    s.close()
+    assert np.all(np.abs(got - A @ x) <= (lens + 1) * 2.0 ** -53 * (absA @ np.abs(x)) * 2.0)   # both sides round
