@@ -236,3 +236,46 @@ def test_batch_rejects_bad_input():
     big = qpgen.make_portfolio(1, n=2049)
     with pytest.raises(HPRQPError, match="ERR_UNSUPPORTED"):
         BS([big])
+
+
+def _dense_rows(q, m, dens, seed):
+    """The same QP with m rows, `dens` of the entries each (row 1 and column 0
+    empty), ranges around A x for an x in the box."""
+    rng = np.random.default_rng(seed)
+    A = np.where(rng.random((m, q.n)) < dens, rng.standard_normal((m, q.n)), 0.0)
+    A[1, :] = 0.0
+    A[:, 0] = 0.0
+    r, c = np.nonzero(A)
+    q.m = m
+    q.a_rowptr = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=m))]).astype(np.int32)
+    q.a_col = c.astype(np.int32)
+    q.a_val = A[r, c]
+    mid = A @ (0.5 * (q.L + np.minimum(q.U, 1.0)))
+    q.l = mid - rng.uniform(0.0, 0.1, m)
+    q.u = mid + rng.uniform(0.0, 0.1, m)
+    q.l[1], q.u[1] = -1.0, 1.0
+    return q
+
+
+@pytest.mark.parametrize("threads,rank", [(0, 10), (0, 16), (64, 10), (512, 16)])
+def test_batch_matrices_in_and_out_of_lds(threads, rank):
+    """A, A^T, c, the box and diag(d) are kept in LDS where they fit: instances
+    with all of it there, with A alone, with neither (more than 12,000 nonzeros,
+    and more than the LDS of the shape), 64 rows, empty rows and columns, on
+    both sides of each bound, in one batch."""
+    BS = _B()
+    cases = [(256, 64, 0.9), (250, 3, 0.5), (512, 64, 0.06), (512, 64, 0.3), (500, 64, 0.4), (1000, 40, 0.08),
+             (1000, 64, 0.19), (1024, 5, 1.0), (1025, 64, 0.12), (2048, 33, 0.2), (2047, 2, 0.1)]
+    qps = [_dense_rows(qpgen.make_portfolio(71_000 + i, n=n, rank=rank), m, d, i) for i, (n, m, d) in enumerate(cases)]
+    b = BS(qps, tol=0.0, max_iter=40, check_every=10, batch_threads=threads)
+    r = b.solve()
+    b.close()
+    for i, q in enumerate(qps):
+        o = oracle.solve(q, tol=0.0, max_iter=40, check_every=10)
+        f = r.infos[i]
+        print(i, q.n, q.m, q.a_val.size, flush=True)
+        assert f["iters"] == o.iters == 40
+        assert f["lambda_A"] == pytest.approx(o.lambda_A, rel=1e-12)
+        assert f["lambda_Q"] == pytest.approx(o.lambda_Q, rel=1e-12)
+        for name, g, ref in (("y", r.y[i], o.y), ("z", r.z[i], o.z), ("w", r.w[i], o.w), ("x", r.x[i], o.x)):
+            assert _rel(g, ref) <= 1e-10, (i, q.n, q.m, name, _rel(g, ref))
