@@ -21,11 +21,13 @@ struct DevParams {
 
 // Scalars derived from DevParams at iteration j of a segment.
 struct IterScalars {
-  double sigma, sQ, kappa, sA, rho;
+  double sigma, sQ, inv, kappa, sA, rho;
   __device__ void load(const DevParams* p, int j) {
     sigma = p->sigma;
     sQ = sigma * p->lamQ;             // sigma lambda_Q
-    kappa = sigma / (1.0 + sQ);       // sigma / (1 + sigma lambda_Q)
+    const double den = __builtin_fma(sigma, p->lamQ, 1.0);
+    inv = 1.0 / den;                  // 1 / (1 + sigma lambda_Q)
+    kappa = sigma / den;              // sigma / (1 + sigma lambda_Q)
     sA = sigma * p->lamA;             // sigma lambda_A
     rho = 1.0 / (double)(p->t0 + j + 2);   // Halpern weight 1/(t+2)
   }

@@ -8,6 +8,22 @@
 #pragma once
 #include "common.hpp"
 
+// The formulas of an iteration that more than one kernel evaluates (one launch
+// per product, one workgroup per segment).  The fused multiply-adds are written
+// out: left to the compiler they differ from kernel to kernel, and so would the
+// last bit of an iterate.
+__device__ __forceinline__ double halpern(double rho, double a, double r) {   // rho a + (1 - rho) r
+  return __builtin_fma(rho, a, (1.0 - rho) * r);
+}
+__device__ __forceinline__ double reflect(double bar, double u) { return __builtin_fma(2.0, bar, -u); }   // 2 bar - u
+__device__ __forceinline__ double y_arg(double av, double sA, double y) { return __builtin_fma(-sA, y, av); }   // r_y
+__device__ __forceinline__ double w_bar(double sQ, double w, double xh, double inv, double kappa, double d) {
+  return __builtin_fma(kappa, d, __builtin_fma(sQ, w, xh) * inv);   // (sQ w + xh) / (1 + sQ) + kappa d
+}
+__device__ __forceinline__ double z_arg(double x, double sigma, double Qw, double ATy, double c) {
+  return __builtin_fma(sigma, ATy - Qw - c, x);   // r_z
+}
+
 // out_i = q_i
 struct EpiStore {
   double* out;
@@ -34,7 +50,7 @@ struct EpiQ1 {
   __device__ __forceinline__ Ops load(int i) const { return Ops{xh[i], ld_stream(Qw + i)}; }
   __device__ __forceinline__ void operator()(int i, double q, double*, const Ops& o) const {
     st_stream(q1 + i, q);                                   // read once, by Q-apply #2
-    v[i] = o.xh + kappa * (o.Qw - q);                       // v is gathered next: keep it cached
+    v[i] = __builtin_fma(kappa, o.Qw - q, o.xh);            // v is gathered next: keep it cached
   }
   __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
 };
@@ -57,10 +73,10 @@ struct EpiY {
   __device__ __forceinline__ void operator()(int i, double q, double* acc) const { (*this)(i, q, acc, load(i)); }
   __device__ __forceinline__ void operator()(int i, double q, double* acc, const Ops& o) const {
     const double yi = o.y, yai = o.ya;
-    const double r = q - sA * yi;
+    const double r = y_arg(q, sA, yi);
     const double yb = (clampd(r, o.l, o.u) - r) / sA;
     ybar[i] = yb;                                            // gathered next by A^T
-    st_stream(y + i, rho * yai + (1.0 - rho) * (2.0 * yb - yi));
+    st_stream(y + i, halpern(rho, yai, reflect(yb, yi)));
     if (want_r) { const double t = yi - yb; acc[0] += t * t; }
     if (want_th) { const double t = yb - yai; acc[1] += t * t; }
   }
@@ -82,7 +98,7 @@ struct EpiAT {
   __device__ __forceinline__ void operator()(int i, double q, double*, const Ops& o) const {
     const double aty = o.aty, atya = o.atya;
     d[i] = q - aty;                                          // gathered next by Q-apply #2
-    st_stream(ATy + i, rho * atya + (1.0 - rho) * (2.0 * q - aty));
+    st_stream(ATy + i, halpern(rho, atya, reflect(q, aty)));
     if (check) { g[i] = q; e[i] = q - atya; }
   }
 };
@@ -110,13 +126,13 @@ struct EpiQ2 {
   double *wbar, *qwbar, *x, *xbar_out;
   int want_r, check, xb_next, trace;
   double l1;                      // lambda of phi (0: the box projection)
-  double sigma, sQ, kappa, rho;
+  double sigma, sQ, inv, kappa, rho;
   static constexpr int NR = 9;
   static constexpr bool PANEL_PREFETCH = true;   // panel-ordered product: prefetch the next chunk
   static constexpr unsigned MAXMASK = 0u;
   __device__ void setup(const DevParams* p, int j) {
     IterScalars s; s.load(p, j);
-    sigma = s.sigma; sQ = s.sQ; kappa = s.kappa; rho = s.rho;
+    sigma = s.sigma; sQ = s.sQ; inv = s.inv; kappa = s.kappa; rho = s.rho;
   }
   // operands loaded early by the panel-ordered product (before its last panel)
   struct Pre { double wa, Qwa, xa; };
@@ -135,9 +151,8 @@ struct EpiQ2 {
   __device__ __forceinline__ void operator()(int i, double q2, double* acc) const { (*this)(i, q2, acc, load(i)); }
   __device__ __forceinline__ void operator()(int i, double q2, double* acc, const Ops& o) const {
     const double xhi = o.xh, wi = o.w, Qwi = o.Qw, di = o.d, wai = o.wa, Qwai = o.Qwa, xai = o.xa;
-    const double inv = 1.0 / (1.0 + sQ);
-    const double wb = (sQ * wi + xhi) * inv + kappa * di;
-    const double Qwb = (sQ * Qwi + o.q1) * inv + kappa * q2;
+    const double wb = w_bar(sQ, wi, xhi, inv, kappa, di);
+    const double Qwb = w_bar(sQ, Qwi, o.q1, inv, kappa, q2);
     if (want_r || check || trace) {
       const double xb = XB[i];
       if (want_r) {
@@ -152,14 +167,14 @@ struct EpiQ2 {
       }
       if (trace) { wbar[i] = wb; xbar_out[i] = xb; }
     }
-    const double xn = rho * xai + (1.0 - rho) * xhi;
-    const double wn = rho * wai + (1.0 - rho) * (2.0 * wb - wi);
-    const double Qwn = rho * Qwai + (1.0 - rho) * (2.0 * Qwb - Qwi);
+    const double xn = halpern(rho, xai, xhi);
+    const double wn = halpern(rho, wai, reflect(wb, wi));
+    const double Qwn = halpern(rho, Qwai, reflect(Qwb, Qwi));
     st_stream(w + i, wn); st_stream(Qw + i, Qwn);
     if (trace) x[i] = xn;
-    const double rz = xn + sigma * (-Qwn + o.ATy - o.c);
+    const double rz = z_arg(xn, sigma, Qwn, o.ATy, o.c);
     const double xbn = prox_phi(rz, sigma * l1, o.L, o.U);
-    xh[i] = 2.0 * xbn - xn;                                  // gathered next by Q-apply #1
+    xh[i] = reflect(xbn, xn);                                // gathered next by Q-apply #1
     if (xb_next) { XB[i] = xbn; ZB[i] = (xbn - rz) / sigma; }
   }
 };

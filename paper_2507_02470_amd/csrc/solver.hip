@@ -735,9 +735,15 @@ SmallArgs small_args(hprqp_handle& h) {
   a.l1 = h.l1;
   a.partials = h.partials; a.counts = h.counts; a.prm = h.dprm;
   // LDS layout: every vector, then row pointers, columns and values of A, A^T, Q
-  long long off = 0;
-  auto take = [&](long long bytes) { const long long o = off; off += (bytes + 15) / 16 * 16; return (int)o; };
-  for (int s = 0; s < SV_COUNT; ++s) a.voff[s] = a.vec[s] ? take(8ll * a.vlen[s]) : 0;
+  // (a zero behind every vector; the path is taken by what the arrays alone need)
+  long long off = 0, need = 0;
+  auto take = [&](long long bytes, int pad = 0) {
+    const long long o = off;
+    off += (bytes + pad + 15) / 16 * 16;
+    need += (bytes + 15) / 16 * 16;
+    return (int)o;
+  };
+  for (int s = 0; s < SV_COUNT; ++s) a.voff[s] = a.vec[s] ? take(8ll * a.vlen[s], 8) : 0;
   const Mat* ms[3] = {&h.A, &h.AT, &h.Q};
   const SmallMat sm[3] = {a.A, a.AT, a.Q};
   for (int q = 0; q < 3; ++q) {
@@ -746,7 +752,7 @@ SmallArgs small_args(hprqp_handle& h) {
     a.moff[q][1] = take(4ll * ms[q]->nnz);
     a.moff[q][2] = take(8ll * ms[q]->nnz);
   }
-  a.lds_bytes = off <= HQ_SMALL_LDS ? (int)off : 0;
+  a.lds_bytes = need <= HQ_SMALL_LDS ? (int)off : 0;
   return a;
 }
 
@@ -769,7 +775,7 @@ void small_attrs() {
                       (const void*)k_small_segment<16, true>, (const void*)k_small_primal<1, true>,
                       (const void*)k_small_primal<2, true>,   (const void*)k_small_primal<4, true>,
                       (const void*)k_small_primal<8, true>,   (const void*)k_small_primal<16, true>};
-  for (const void* k : ks) HQC(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, HQ_SMALL_LDS));
+  for (const void* k : ks) HQC(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, HQ_SMALL_LDS + 16 * SV_COUNT));
 }
 
 void enqueue_small_segment(hprqp_handle& h, int Tseg) {
@@ -1424,8 +1430,8 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
       const bool on = ok && (opt->small_path == 1 || (opt->small_path == -1 && small_args(h).lds_bytes > 0));
       if (on) {
         // the most lanes per row with which one pass of the workgroup covers
-        // every row (small CCQP, n = 200: 4 lanes 6.9 us/iteration, 2 lanes
-        // 7.3, 8 lanes 7.9)
+        // every row (small CCQP, n = 200, in phases: 4 lanes 6.9 us/iteration,
+        // 2 lanes 7.3, 8 lanes 7.9)
         int G = 1;
         while (G < 16 && (long long)std::max(n, m) * G * 2 <= HQ_SMALL_BS) G *= 2;
         h.small_G = G;

@@ -154,3 +154,58 @@ def test_small_path_options():
         s.close()
     np.testing.assert_array_equal(out[0].check_log[:, 7], out[1].check_log[:, 7])
     assert _max_rel(out[1].x.cpu().numpy(), out[0].x.cpu().numpy()) <= 1e-12
+
+
+def _sparse(n, m, seed):
+    """Diagonally dominant sparse Q, four entries a row of A, and one full row of each."""
+    import scipy.sparse as sp
+    rng = np.random.default_rng(seed)
+    B = sp.random(n, n, 3.0 / n, random_state=rng, data_rvs=lambda k: rng.standard_normal(k)).tolil()
+    B[0, :] = 0.01 * rng.standard_normal(n)
+    Q = (B + B.T).tocsr()
+    Q = (Q + sp.diags(np.abs(Q).sum(axis=1).A1 + 0.1)).tocsr()
+    A = sp.random(m, n, 4.0 / n, random_state=rng, data_rvs=lambda k: rng.standard_normal(k)).tolil()
+    A[m - 1, :] = rng.standard_normal(n)
+    A = A.tocsr()
+    for M in (Q, A):
+        M.sort_indices()
+    i32 = np.int32
+    return qpgen.QP(n=n, m=m, qkind="csr", c=rng.standard_normal(n), L=np.full(n, -2.0), U=np.full(n, 2.0),
+                    a_rowptr=A.indptr.astype(i32), a_col=A.indices.astype(i32), a_val=A.data,
+                    l=np.full(m, -1.0), u=np.full(m, 1.0),
+                    q_rowptr=Q.indptr.astype(i32), q_col=Q.indices.astype(i32), q_val=Q.data)
+
+
+@pytest.mark.parametrize("name,make", [
+    ("small_ccqp", lambda: qpgen.make_small_ccqp()),
+    ("n24", lambda: qpgen.make_tiny(11, n=24, m=5)),
+    ("n64", lambda: qpgen.make_tiny(12, n=64, m=40)),
+    ("m0", lambda: qpgen.make_tiny(4, n=6, m=0)),
+    ("zeroQ", lambda: qpgen.make_tiny(5, n=8, m=4, qkind="zero")),
+    ("l1", lambda: _l1(qpgen.make_tiny(6, n=7, m=3, n_eq=1), 0.3)),
+    ("tall", lambda: _sparse(40, 300, 1)),
+    ("n257", lambda: _sparse(257, 100, 2)),
+    ("n400", lambda: _sparse(400, 100, 3)),
+    ("m1200", lambda: _sparse(20, 1200, 4)),
+])
+def test_iterations_between_checks_are_those_of_checked_segments(name, make):
+    """The iterations of a segment without reductions or outputs run from registers;
+    with a check after every one none does.  Without restarts the iterates of the
+    two are bit-identical (rows with more entries than the registers hold, every
+    number of lanes per row, no rows, Q = 0, an l1 term, and more rows than
+    threads, where both take the phases)."""
+    DP, Solver = _S()
+    qp = make()
+    dp = DP(qp)
+    out = []
+    for T in (1, 3, 4, 40):
+        s = Solver(dp, lambda_A=30.0 if qp.m else 0.0, lambda_Q=20.0 if qp.qkind != "zero" else 0.0, tol=0.0,
+                   max_iter=80, check_every=T, enable_restart=0, enable_sigma_update=0, small_path=1)
+        r = s.solve()
+        s.close()
+        assert r.iters == 80
+        out.append([getattr(r, k).cpu().numpy() for k in ("y", "z", "w", "x")])
+    assert np.all(np.isfinite(out[0][3])) and np.max(np.abs(out[0][3])) > 0.0
+    for o in out[1:]:
+        for a, b in zip(o, out[0]):
+            np.testing.assert_array_equal(a, b)
