@@ -184,3 +184,34 @@ def test_power_method_over_scales_and_starts(scale, start):
             break
     assert info["it_A"] == it
     assert abs(info["est_A"] - lam) <= 2 * (6 * it + 2 * n + 10) * 2.0 ** -53 * lam
+
+
+def test_chunk_that_overflows_leaves_nothing_for_a_solve_without_rows():
+    """A chunk of the power method that overflows leaves infinities in the
+    reduction slots; without rows a solve never writes some of them, and reads
+    them as 0: the same result as with lambda_Q given (a run of its own, with no
+    power method)."""
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    n, big = 64, 1e30
+    q = np.random.default_rng(2).uniform(0.5, 1.0, n)
+    q[5] = big
+    v0 = np.ones(n)
+    v0[5] = 1e-3 / big
+    qp = qpgen.QP(n=n, m=0, qkind="csr", c=np.linspace(-1.0, 1.0, n), L=np.full(n, -2.0), U=np.full(n, 2.0),
+                  a_rowptr=np.zeros(1, np.int32), a_col=np.zeros(0, np.int32), a_val=np.zeros(0),
+                  l=np.zeros(0), u=np.zeros(0), q_rowptr=np.arange(n + 1, dtype=np.int32),
+                  q_col=np.arange(n, dtype=np.int32), q_val=q)
+    for small in (0, 1):
+        kw = dict(tol=0.0, max_iter=60, check_every=20, small_path=small, sigma0=1.0)
+        s = Solver(DeviceProblem(qp), power_start_Q=v0, **kw)
+        a = s.solve()
+        s.close()
+        assert a.lambda_Q == pytest.approx(1.01 * big, rel=1e-12)
+        s = Solver(DeviceProblem(qp), lambda_Q=a.lambda_Q, **kw)
+        b = s.solve()
+        s.close()
+        print("small_path", small, a.term, a.sigma, b.term, b.sigma, flush=True)
+        assert a.term == b.term and a.iters == b.iters and a.sigma == b.sigma
+        assert np.isfinite(a.sigma)
+        for k in ("x", "w", "z"):
+            assert torch.equal(getattr(a, k), getattr(b, k)), k
