@@ -505,6 +505,12 @@ void launch_elem(hprqp_handle& h, int n, const double* q, const Epi& epi, int j,
 void final_reduce(hprqp_handle& h, int slot0, int nslot) {
   k_final_reduce<<<nslot, 256, 0, h.st>>>(h.partials, h.counts, slot0, kMaxMask, h.scalars);
 }
+// The same into the pinned host array h.hs, which the host reads after its next
+// wait for the stream: a copy of the few scalars is a launch of its own (5 us and
+// the gap before it).
+void final_reduce_host(hprqp_handle& h, int slot0, int nslot, unsigned long long maxmask = kMaxMask) {
+  k_final_reduce<<<nslot, 256, 0, h.st>>>(h.partials, h.counts, slot0, maxmask, h.hs);
+}
 
 inline int tile_count(int M, int N, int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); }
 
@@ -633,8 +639,7 @@ void q_apply(hprqp_handle& h, const double* x, const Epi& epi, int j, const RedO
 double qwx_norm(hprqp_handle& h, const double* wv, const double* xv) {
   k_diff<<<hq_grid(h.n, 256), 256, 0, h.st>>>(h.n, wv, xv, nullptr, h.t1);
   q_apply(h, h.t1, EpiMaxAbs{h.pre ? h.iDs : nullptr}, 0, red_seq(h, SL_QWX, 1));
-  final_reduce(h, SL_QWX, 1);
-  HQC(hipMemcpyAsync(h.hs + SL_QWX, h.scalars + SL_QWX, sizeof(double), hipMemcpyDeviceToHost, h.st));
+  final_reduce_host(h, SL_QWX, 1);
   HQC(hipStreamSynchronize(h.st));
   return h.hs[SL_QWX];
 }
@@ -787,8 +792,7 @@ void enqueue_small_segment(hprqp_handle& h, int Tseg) {
     case 8: launch_small<8>(h, a, Tseg); break;
     default: launch_small<16>(h, a, Tseg); break;
   }
-  final_reduce(h, 0, SL_ITER_END);
-  HQC(hipMemcpyAsync(h.hs, h.scalars, SL_ITER_END * sizeof(double), hipMemcpyDeviceToHost, h.st));
+  final_reduce_host(h, 0, SL_ITER_END);
 }
 
 // one workgroup per segment: chosen at create, and used while the data of
@@ -801,8 +805,7 @@ void enqueue_segment(hprqp_handle& h, int Tseg, bool prof) {
     return;
   }
   for (int j = 0; j < Tseg; ++j) enqueue_iter(h, j, Tseg, false, prof);
-  final_reduce(h, 0, SL_ITER_END);
-  HQC(hipMemcpyAsync(h.hs, h.scalars, SL_ITER_END * sizeof(double), hipMemcpyDeviceToHost, h.st));
+  final_reduce_host(h, 0, SL_ITER_END);
 }
 
 void stage1(hprqp_handle& h) {
@@ -890,8 +893,7 @@ double power_method(hprqp_handle& h, int which, const double* start, int maxit, 
   if (k == 0) { if (iters_out) *iters_out = 0; return 0.0; }
   constexpr int CHUNK = SL_ITER_END / 2;                     // iterations per chunk: 2 slots each, all sums
   auto reduce_to_host = [&](int slots) {
-    k_final_reduce<<<slots, 256, 0, h.st>>>(h.partials, h.counts, 0, 0ull, h.scalars);
-    HQC(hipMemcpyAsync(h.hs, h.scalars, slots * sizeof(double), hipMemcpyDeviceToHost, h.st));
+    final_reduce_host(h, 0, slots, 0ull);
     HQC(hipStreamSynchronize(h.st));
   };
   double* const base = which == 0 ? h.ya : h.g;              // a chunk's start, |base|^2 = 1 up to rounding
@@ -944,9 +946,6 @@ double power_method(hprqp_handle& h, int which, const double* start, int maxit, 
     len = first || L > 1 || len == 1 ? CHUNK : 1;             // after a failed chunk: one by one, then chunks again
   }
   if (iters_out) *iters_out = stop_it < 0 ? maxit : stop_it;
-  // the slots were the iteration's: one that a solve without rows never writes must
-  // read as 0, not as a partial of a chunk that overflowed
-  k_zero_ints<<<1, 64, 0, h.st>>>(SL_ITER_END, h.counts);
   return lam;
 }
 
@@ -1507,22 +1506,21 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
     if (m > 0) launch_elem(h, m, nullptr, EpiNormB{h.l, h.u}, 0, red_seq(h, SL_NRM, 2));
     launch_elem(h, n, nullptr, EpiNormC{h.c}, 0, red_seq(h, SL_NRM + 2, 2));
     // EpiNormC writes (sum c^2, max|c|) into slots NRM+2, NRM+3
-    final_reduce(h, SL_NRM, 4);
-    HQC(hipMemcpyAsync(h.hs, h.scalars + SL_NRM, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+    final_reduce_host(h, SL_NRM, 4);
     HQC(hipStreamSynchronize(st));
-    const double nb = m > 0 ? std::sqrt(h.hs[0]) : 0.0, nc = std::sqrt(h.hs[2]);
-    h.binf = m > 0 ? h.hs[1] : 0.0;
-    h.cinf = h.hs[3];
+    const double* const hn = h.hs + SL_NRM;
+    const double nb = m > 0 ? std::sqrt(hn[0]) : 0.0, nc = std::sqrt(hn[2]);
+    h.binf = m > 0 ? hn[1] : 0.0;
+    h.cinf = hn[3];
     if (h.pre) {
       // sigma0 uses the scaled b and c (the problem the method runs on); the
       // stopping test uses the norms of the given problem
       if (m > 0) launch_elem(h, m, nullptr, EpiNormB{h.l0, h.u0}, 0, red_seq(h, SL_NRM, 2));
       launch_elem(h, n, nullptr, EpiNormC{h.c0}, 0, red_seq(h, SL_NRM + 2, 2));
-      final_reduce(h, SL_NRM, 4);
-      HQC(hipMemcpyAsync(h.hs, h.scalars + SL_NRM, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+      final_reduce_host(h, SL_NRM, 4);
       HQC(hipStreamSynchronize(st));
-      h.binf = m > 0 ? h.hs[1] : 0.0;
-      h.cinf = h.hs[3];
+      h.binf = m > 0 ? hn[1] : 0.0;
+      h.cinf = hn[3];
     }
     const bool norms_ok = nb >= 1e-16 && nb <= 1e16 && nc >= 1e-16 && nc <= 1e16;
     if (opt->sigma0 > 0) h.sigma0 = opt->sigma0;
@@ -1610,8 +1608,7 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
         enqueue_iter(h, j, Tseg, true, false);
         if (j < Tseg - 1 && k + j + 1 <= o.trace_iters) trace_row(h, o.trace_host + (size_t)(k + j) * rowlen);
       }
-      final_reduce(h, 0, SL_ITER_END);
-      HQC(hipMemcpyAsync(h.hs, h.scalars, SL_ITER_END * sizeof(double), hipMemcpyDeviceToHost, h.st));
+      final_reduce_host(h, 0, SL_ITER_END);
     } else if (o.use_graph && Tseg == T && !prof) {
       if (!h.gexec || h.graph_T != T) {
         if (h.gexec) { hipGraphExecDestroy(h.gexec); h.gexec = nullptr; }
@@ -1807,8 +1804,7 @@ void enqueue_primal_segment(hprqp_handle& h, int Tseg, bool prof) {
     return;
   }
   for (int j = 0; j < Tseg; ++j) enqueue_primal_iter(h, j, Tseg, false, prof);
-  final_reduce(h, 0, SL_ITER_END);
-  HQC(hipMemcpyAsync(h.hs, h.scalars, SL_ITER_END * sizeof(double), hipMemcpyDeviceToHost, h.st));
+  final_reduce_host(h, 0, SL_ITER_END);
 }
 
 // ||du||_M from the merit slots, metric of Algorithm 6 / 7
@@ -1878,8 +1874,7 @@ void solve_primal_impl(hprqp_handle& h, const double* y0, const double* w0, cons
         enqueue_primal_iter(h, j, Tseg, true, false);
         if (j < Tseg - 1 && k + j + 1 <= o.trace_iters) primal_trace_row(h, o.trace_host + (size_t)(k + j) * rowlen);
       }
-      final_reduce(h, 0, SL_ITER_END);
-      HQC(hipMemcpyAsync(h.hs, h.scalars, SL_ITER_END * sizeof(double), hipMemcpyDeviceToHost, h.st));
+      final_reduce_host(h, 0, SL_ITER_END);
     } else if (o.use_graph && Tseg == T && !prof) {
       if (!h.pgexec || h.pgraph_T != T || h.pgraph_method != meth) {
         if (h.pgexec) { hipGraphExecDestroy(h.pgexec); h.pgexec = nullptr; }
@@ -1984,8 +1979,6 @@ void residuals_impl(hprqp_handle& h, const double* y, const double* z, const dou
                     hprqp_info* info) {
   if (!z || !x || (h.m > 0 && !y) || !info) fail(HPRQP_ERR_ARG, "NULL argument");
   const double* const x_given = x;   // x below becomes the scaled copy when preconditioned
-  write_params(h, h.sigma0, 0);
-  k_zero_ints<<<1, 64, 0, h.st>>>(SL_ITER_END, h.counts);
   if (h.pre) {
     // the point is given in the original variables: scale it (y/E, z D, x/D)
     // and take the stopping quantities as at a check
@@ -2000,27 +1993,22 @@ void residuals_impl(hprqp_handle& h, const double* y, const double* z, const dou
   }
   q_apply(h, x, EpiResQ{x, z, h.m > 0 ? h.t2 : nullptr, h.c, h.L, h.U, nullptr, nullptr, h.iDs, h.l1}, 0,
           red_seq(h, SL_RQ, 7));
-  final_reduce(h, 0, SL_ITER_END);
-  HQC(hipMemcpyAsync(h.hs, h.scalars, SL_ITER_END * sizeof(double), hipMemcpyDeviceToHost, h.st));
-  HQC(hipStreamSynchronize(h.st));
-  const Resid r = residuals_from(h, h.hs);
-  std::memset(info, 0, sizeof(*info));
-  info->eta_p = r.eta_p; info->eta_d = r.eta_d; info->eta_gap = r.eta_gap; info->pobj = r.pobj; info->dobj = r.dobj;
-  info->qwx_gap = std::numeric_limits<double>::quiet_NaN();
   if (w) {
     // Q (w - x) of the given problem: with preconditioning, (w - x)/D in the scaled variables
     k_diff<<<hq_grid(h.n, 256), 256, 0, h.st>>>(h.n, w, x_given, h.pre ? h.iDs : nullptr, h.t2);
     q_apply(h, h.t2, EpiMaxAbs{h.pre ? h.iDs : nullptr}, 0, red_seq(h, SL_QWX, 1));
-    final_reduce(h, SL_QWX, 1);
-    HQC(hipMemcpyAsync(h.hs + SL_QWX, h.scalars + SL_QWX, sizeof(double), hipMemcpyDeviceToHost, h.st));
-    HQC(hipStreamSynchronize(h.st));
-    info->qwx_gap = h.hs[SL_QWX];
   }
+  // one wait for all of it (a slot without partials of this call is not read)
+  final_reduce_host(h, SL_RA, (w ? SL_TOTAL : SL_ITER_END) - SL_RA);
+  HQC(hipStreamSynchronize(h.st));
+  const Resid r = residuals_from(h, h.hs);
+  std::memset(info, 0, sizeof(*info));
+  info->eta_p = r.eta_p; info->eta_d = r.eta_d; info->eta_gap = r.eta_gap; info->pobj = r.pobj; info->dobj = r.dobj;
+  info->qwx_gap = w ? h.hs[SL_QWX] : std::numeric_limits<double>::quiet_NaN();
 }
 
 void apply_impl(hprqp_handle& h, int op, const double* in, double* out) {
   if (!in || !out) fail(HPRQP_ERR_ARG, "NULL argument");
-  write_params(h, h.sigma0, 0);
   // the operators of the problem as given (the unscaled copies when preconditioned)
   if (op == 0 && h.pre && h.qkind == HPRQP_Q_CSR) launch_csr(h, h.Q0, in, EpiStore{out}, 0, no_red(h));
   else if (op == 0) q_apply(h, in, EpiStore{out}, 0, no_red(h));
