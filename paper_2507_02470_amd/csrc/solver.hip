@@ -388,7 +388,8 @@ void launch_xrow_g(hprqp_handle& h, const Mat& M, const double* x, const Epi& ep
   const long long passes = ((long long)M.rows + BS - 1) / BS;   // 64 rows per wave
   const int grid = (int)std::max(1ll, std::min(passes, (long long)std::min(h.ncu * per_cu, HQ_GRID_CAP)));
   check_red_grid(grid, red);
-  k_csr_xrow<G, Epi><<<grid, BS, lds, h.st>>>(M.rows, M.rp, M.c16, M.v, x, epi, h.dprm, j, red, M.cols);
+  k_csr_xrow<G, Epi><<<grid, BS, lds, h.st>>>(M.rows, M.rp, M.c16, M.v, x, epi, h.dprm, j, red, M.cols,
+                                           (int)M.nnz);
 }
 
 template <class Epi>
@@ -448,7 +449,16 @@ void launch_csr_stream(hprqp_handle& h, const Mat& M, const double* x, const Epi
 template <class Epi>
 void launch_csr(hprqp_handle& h, const Mat& M, const double* x, const Epi& epi, int j, const RedOut& red) {
   if (M.G == HQ_G_XLDS) { launch_csr_xlds(h, M, x, epi, j, red); return; }
-  if (is_xrow(M.G)) { launch_csr_xrow(h, M, x, epi, j, red); return; }
+  if (is_xrow(M.G)) {
+    if (M.nnz < 2) {   // (that kernel reads entries in pairs)
+      Mat one = M;
+      one.G = 1;
+      launch_csr(h, one, x, epi, j, red);
+      return;
+    }
+    launch_csr_xrow(h, M, x, epi, j, red);
+    return;
+  }
   if (M.G == HQ_G_SPLIT) { launch_split(h, M, x, epi, j, red); return; }
   if (M.G == HQ_G_PANEL) {
     // row blocks per workgroup: the fewest for which the whole grid is
@@ -952,8 +962,8 @@ double power_method(hprqp_handle& h, int which, const double* start, int maxit, 
 // 16-bit columns of M for the row-split kernel gathering from LDS
 void build_c16(hprqp_handle& h, Mat& M) {
   if (M.c16 || M.rows == 0 || M.nnz == 0 || M.cols > HQ_XLDS_MAX) return;
-  unsigned short* c = h.dalloc<unsigned short>((size_t)M.nnz);
-  k_cols16<<<hq_grid(M.nnz, 256), 256, 0, h.st>>>(M.nnz, M.ci, c);
+  unsigned short* c = h.dalloc<unsigned short>((size_t)M.nnz + 1);
+  k_cols16<<<hq_grid(M.nnz + 1, 256), 256, 0, h.st>>>(M.nnz, M.ci, c);
   M.c16 = c;
 }
 

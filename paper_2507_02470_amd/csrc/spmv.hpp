@@ -211,11 +211,13 @@ __global__ __launch_bounds__(BS) void k_csr_xstream(int nrows, const int* __rest
   if (red.active) block_reduce_store<NR, Epi::MAXMASK>(acc, red);
 }
 
-// 16-bit copy of the columns of a matrix whose input vector fits LDS
+// 16-bit copy of the columns of a matrix whose input vector fits LDS, and a zero
+// behind them (they are read in pairs)
 __global__ void k_cols16(long long nnz, const int* __restrict__ col, unsigned short* __restrict__ c16) {
-  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < nnz; k += (long long)gridDim.x * blockDim.x)
-    c16[k] = (unsigned short)col[k];
+  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k <= nnz; k += (long long)gridDim.x * blockDim.x)
+    c16[k] = k < nnz ? (unsigned short)col[k] : 0;
 }
+typedef double hq_pair __attribute__((ext_vector_type(2), aligned(8)));   // two entries' values
 
 // Row-split kernel (G <= 64 lanes per row) gathering from an LDS copy of the input
 // vector (at most HQ_XLDS_MAX entries): for rows of tens to hundreds of nonzeros
@@ -227,10 +229,12 @@ __global__ void k_cols16(long long nnz, const int* __restrict__ col, unsigned sh
 // gives lane l the sum of row l for the epilogue.
 // Bound by the stream of the matrix, which needs some 40 KB in flight per CU beside
 // the 16 waves that the vector's copy leaves room for: 10 bytes an entry
-// (16-bit columns), eight entries a lane, the next row's loads issued before the
-// current row is summed, the row pointers of all G rows loaded at once.
-// Ahat^T of the Lasso (5e5 rows of 100 over 1e4 columns): 165 -> 140 us a plain
-// product; with the iteration's epilogue 192 + 14 us for the step behind it -> 150.
+// (16-bit columns), eight entries a lane in four pairs (16- and 4-byte loads; one
+// entry a load kept the address units busy), the next row's loads issued before
+// the current row is summed, the row pointers of all G rows loaded at once.
+// Ahat^T of the Lasso (5e5 rows of 100 over 1e4 columns), 500 MB: 165 us with 32-bit
+// columns, 140 with 16-bit ones, 107 in pairs (4.7 TB/s, the rate of a large copy);
+// with the iteration's epilogue 192 + 14 us for the step behind it, 150, 121.
 #define HQ_XROW_U 8
 template <int G, class Epi>
 __global__ __launch_bounds__(HQ_XLDS_BLOCK) void k_csr_xrow(int nrows, const int* __restrict__ rowptr,
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(HQ_XLDS_BLOCK) void k_csr_xrow(int nrows, const int
                                                             const double* __restrict__ val,
                                                             const double* __restrict__ xin, Epi epi,
                                                             const DevParams* __restrict__ prm, int j, RedOut red,
-                                                            int ncols) {
+                                                            int ncols, int nnz) {
   static_assert(G >= 1 && G <= HQ_WAVE && (HQ_WAVE % G) == 0, "lanes per row");
   constexpr int BS = HQ_XLDS_BLOCK, WAVES = BS / HQ_WAVE, U = HQ_XROW_U;
   constexpr int NR = Epi::NR;
@@ -252,32 +256,41 @@ __global__ __launch_bounds__(HQ_XLDS_BLOCK) void k_csr_xrow(int nrows, const int
   for (int s = 0; s < (NR > 0 ? NR : 1); ++s) acc[s] = 0.0;
   for (int i = threadIdx.x; i < ncols; i += BS) xs[i] = xin[i];
   __syncthreads();
-  struct Row { int b, en, c[U]; double v[U]; };
+  struct Row { int b, en; unsigned c[U / 2]; hq_pair v[U / 2]; };
   const long long chunks = ((long long)nrows + HQ_WAVE - 1) / HQ_WAVE;
   for (long long ch = (long long)blockIdx.x * WAVES + threadIdx.x / HQ_WAVE; ch < chunks;
        ch += (long long)gridDim.x * WAVES) {   // same trip count in every lane of the wave
     const int row = (int)(ch * HQ_WAVE) + lane, rc = min(row, nrows - 1);
     const int rb = rowptr[rc], re = row < nrows ? rowptr[rc + 1] : rb;
-    // the first U entries per lane of the group's row of step q (clamped into the
-    // row, an empty row to the entry before it: read, never used)
+    // the first U entries per lane of the group's row of step q, in pairs k, k + 1 of
+    // even k (clamped into the row, an empty row to the entry before it: read, never
+    // used; the last entry of an odd number of them is the second of its pair)
+    auto first = [&](const Row& r) { return (r.b & ~1) + 2 * gl; };
     auto fetch = [&](int q, Row& r) {
       r.b = __shfl(rb, q * NG + gi);
       r.en = __shfl(re, q * NG + gi);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = max(min(r.b + gl + u * G, r.en - 1), 0);
-        r.c[u] = ld_stream(c16 + k);
-        r.v[u] = ld_stream(val + k);
+      for (int u = 0; u < U / 2; ++u) {
+        const int k = max(min(first(r) + 2 * u * G, (r.en - 1) & ~1), 0);
+        r.c[u] = __builtin_nontemporal_load((const unsigned*)(c16 + k));
+        r.v[u] = __builtin_nontemporal_load((const hq_pair*)(val + min(k, nnz - 2)));
       }
     };
     double mine = 0.0;
     auto sum = [&](int q, const Row& r) {
       double s = 0.0, x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = xs[r.c[u]];
+      for (int u = 0; u < U / 2; ++u) { x[2 * u] = xs[r.c[u] & 0xffffu]; x[2 * u + 1] = xs[r.c[u] >> 16]; }
 #pragma unroll
-      for (int u = 0; u < U; ++u) s += r.v[u] * (r.b + gl + u * G < r.en ? x[u] : 0.0);
-      for (int k = r.b + gl + U * G; k < r.en; k += G) s += ld_stream(val + k) * xs[ld_stream(c16 + k)];
+      for (int u = 0; u < U / 2; ++u) {
+        const int k = first(r) + 2 * u * G;
+        s += (k == nnz - 1 ? r.v[u].y : r.v[u].x) * (k >= r.b && k < r.en ? x[2 * u] : 0.0);
+        s += r.v[u].y * (k + 1 < r.en ? x[2 * u + 1] : 0.0);
+      }
+      for (int k = first(r) + U * G; k < r.en; k += 2 * G) {
+        s += ld_stream(val + k) * xs[ld_stream(c16 + k)];
+        if (k + 1 < r.en) s += ld_stream(val + k + 1) * xs[ld_stream(c16 + k + 1)];
+      }
       s = group_sum<G>(s);
       if (gl == q) mine = s;
     };

@@ -169,3 +169,28 @@ def test_row_split_products_from_lds(rows, cols, avg, g):
     got = s.apply("A", x).cpu().numpy()
     s.close()
     assert np.all(np.abs(got - A @ x) <= (lens + 1) * 2.0 ** -53 * (absA @ np.abs(x)) * 2.0)   # both sides round
+
+
+@pytest.mark.parametrize("lens", [[1], [0, 1, 0], [2], [1, 2], [1, 1, 1], [0, 5, 0, 3, 1], [33, 0, 32, 1, 31, 64],
+                                  [300, 1, 257, 0, 129, 1]])
+@pytest.mark.parametrize("g", [1, 16, 64])
+def test_row_split_products_read_entries_in_pairs(lens, g):
+    """The row-split kernel over LDS reads pairs of entries that start at even
+    positions: rows that begin or end inside a pair, a matrix of one entry, an odd
+    number of entries (the last has no partner), entries past those in flight.
+    Bound as above."""
+    import scipy.sparse as sp
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    rows, cols = len(lens), 37
+    rng = np.random.default_rng(sum(lens))
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    ci, v = rng.integers(0, cols, rp[-1]), rng.standard_normal(rp[-1])
+    print(f"pairs lens={lens} g={g}", flush=True)
+    qp = qpgen.QP(n=cols, m=rows, qkind="zero", c=np.ones(cols), L=np.zeros(cols), U=np.ones(cols), a_rowptr=rp,
+                  a_col=ci, a_val=v, l=np.zeros(rows), u=np.ones(rows))
+    s = Solver(DeviceProblem(qp), lambda_A=1.0, tol=0.0, max_iter=1, spmv_lanes=-100 - g, small_path=0)
+    A, absA = (sp.csr_matrix((w, ci.copy(), rp.copy()), shape=(rows, cols)) for w in (v.copy(), np.abs(v)))
+    x = rng.standard_normal(cols)
+    got = s.apply("A", x).cpu().numpy()
+    s.close()
+    assert np.all(np.abs(got - A @ x) <= (np.array(lens) + 1) * 2.0 ** -53 * (absA @ np.abs(x)) * 2.0)
