@@ -956,6 +956,9 @@ double power_method(hprqp_handle& h, int which, const double* start, int maxit, 
     len = first || L > 1 || len == 1 ? CHUNK : 1;             // after a failed chunk: one by one, then chunks again
   }
   if (iters_out) *iters_out = stop_it < 0 ? maxit : stop_it;
+  // the slots were the iteration's: one that a solve without rows never writes must
+  // read as 0, not as a partial of a chunk that overflowed
+  k_zero_ints<<<1, 64, 0, h.st>>>(SL_ITER_END, h.counts);
   return lam;
 }
 

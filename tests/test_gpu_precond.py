@@ -215,3 +215,43 @@ def test_chunk_that_overflows_leaves_nothing_for_a_solve_without_rows():
         assert np.isfinite(a.sigma)
         for k in ("x", "w", "z"):
             assert torch.equal(getattr(a, k), getattr(b, k)), k
+
+
+@pytest.mark.parametrize("kind", ["gram", "csr", "csr_small", "zero"])
+def test_estimates_leave_nothing_in_the_slots_of_a_solve(kind):
+    """The power method uses the reduction slots of an iteration; a solve without
+    rows, or with Q = 0, never writes some of them and reads them as 0.  A solve
+    that takes its own estimates equals, to the last bit and over its restarts,
+    one that is given the same lambdas."""
+    import scipy.sparse as sp
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    rng = np.random.default_rng(11)
+    n, i32 = 400, np.int32
+    none = dict(a_rowptr=np.zeros(1, i32), a_col=np.zeros(0, i32), a_val=np.zeros(0), l=np.zeros(0), u=np.zeros(0))
+    if kind == "gram":
+        qp = qpgen.make_lasso(seed=3, p=60, q=n)
+    elif kind == "zero":
+        qp = qpgen.make_tiny(5, n=8, m=4, qkind="zero")
+    else:
+        B = sp.random(n, n, 0.02, random_state=rng, data_rvs=rng.standard_normal)
+        Q = (B @ B.T + 0.01 * sp.eye(n)).tocsr()
+        Q.sort_indices()
+        qp = qpgen.QP(n=n, m=0, qkind="csr", c=rng.standard_normal(n), L=np.full(n, -2.0), U=np.full(n, 2.0),
+                      q_rowptr=Q.indptr.astype(i32), q_col=Q.indices.astype(i32), q_val=Q.data, **none)
+    kw = dict(tol=0.0, max_iter=600, check_every=20, log_cap=100, sigma0=1.0, small_path=int(kind == "csr_small"))
+    if kind == "gram":
+        kw.pop("small_path")
+    dp = DeviceProblem(qp)
+    s = Solver(dp, **kw)
+    a = s.solve()
+    s.close()
+    lam = dict(lambda_Q=a.lambda_Q) if qp.qkind != "zero" else {}
+    if qp.m:
+        lam["lambda_A"] = a.lambda_A
+    s = Solver(dp, **lam, **kw)
+    b = s.solve()
+    s.close()
+    assert a.restarts > 1
+    np.testing.assert_array_equal(a.check_log, b.check_log)
+    for k in ("x", "w", "z"):
+        assert torch.equal(getattr(a, k), getattr(b, k)), k
