@@ -122,6 +122,31 @@ __global__ void k_mul(long long n, const double* __restrict__ s, const double* _
     o[i] = s[i] * f[i];
 }
 
+// Several vectors at once (the start of a solve, a restart, the outputs: each a
+// launch of its own otherwise), and the iteration scalars (prm NULL: none)
+struct Moves {
+  struct {
+    long long n;
+    const double *src, *f;   // dst = src f (src NULL: 0; f NULL: 1)
+    double *dst, *dst2;      // (dst2 NULL: none)
+  } m[8];
+  int k = 0;
+  void add(long long n, const double* src, const double* f, double* dst, double* dst2 = nullptr) {
+    if (n > 0) { auto& q = m[k++]; q.n = n; q.src = src; q.f = f; q.dst = dst; q.dst2 = dst2; }
+  }
+};
+__global__ void k_moves(Moves a, DevParams p, DevParams* __restrict__ prm) {
+  if (prm && blockIdx.x == 0 && threadIdx.x == 0) *prm = p;
+  for (int q = 0; q < a.k; ++q) {
+    const auto& m = a.m[q];
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < m.n; i += (long long)gridDim.x * blockDim.x) {
+      const double v = m.src ? (m.f ? m.src[i] * m.f[i] : m.src[i]) : 0.0;
+      m.dst[i] = v;
+      if (m.dst2) m.dst2[i] = v;
+    }
+  }
+}
+
 __global__ void k_recip(long long n, const double* __restrict__ s, double* __restrict__ o) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
     o[i] = 1.0 / s[i];
@@ -276,7 +301,7 @@ struct hprqp_handle {
   DevParams* dprm = nullptr;
   // pinned host
   double* hs = nullptr;      // scalars
-  DevParams* hp = nullptr;   // params
+  hipEvent_t ev_done = nullptr;   // the outputs of a solve
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
   int graph_T = 0;
@@ -305,7 +330,7 @@ struct hprqp_handle {
     if (pgraph) hipGraphDestroy(pgraph);
     for (void* p : owned) hipFree(p);
     if (hs) hipHostFree(hs);
-    if (hp) hipHostFree(hp);
+    if (ev_done) hipEventDestroy(ev_done);
     if (own_st) hipStreamDestroy(own_st);
     for (auto& a : pev)
       for (auto& b : a)
@@ -646,21 +671,24 @@ void q_apply(hprqp_handle& h, const double* x, const Epi& epi, int j, const RedO
 // method runs on (the scaled ones when preconditioned: Q D (w~ - x~) =
 // D^-1 Q~ (w~ - x~)).  At a solution the shadow w_Q and x differ by an
 // element of ker Q (Proposition 2.4), so this is 0 up to rounding there.
-double qwx_norm(hprqp_handle& h, const double* wv, const double* xv) {
+void enqueue_qwx(hprqp_handle& h, const double* wv, const double* xv) {
   k_diff<<<hq_grid(h.n, 256), 256, 0, h.st>>>(h.n, wv, xv, nullptr, h.t1);
   q_apply(h, h.t1, EpiMaxAbs{h.pre ? h.iDs : nullptr}, 0, red_seq(h, SL_QWX, 1));
   final_reduce_host(h, SL_QWX, 1);
+}
+double qwx_norm(hprqp_handle& h, const double* wv, const double* xv) {
+  enqueue_qwx(h, wv, xv);
   HQC(hipStreamSynchronize(h.st));
   return h.hs[SL_QWX];
 }
 
-void write_params(hprqp_handle& h, double sigma, long long t0) {
-  h.hp->sigma = sigma;
-  h.hp->lamA = h.lamA;
-  h.hp->lamQ = h.lamQ;
-  h.hp->t0 = t0;
-  HQC(hipMemcpyAsync(h.dprm, h.hp, sizeof(DevParams), hipMemcpyHostToDevice, h.st));
+// vectors moved and the iteration scalars set in one launch
+void moves_and_params(hprqp_handle& h, const Moves& mv, double sigma, long long t0) {
+  long long most = 1;
+  for (int q = 0; q < mv.k; ++q) most = std::max(most, mv.m[q].n);
+  k_moves<<<hq_grid(most, 256), 256, 0, h.st>>>(mv, DevParams{sigma, h.lamA, h.lamQ, t0}, h.dprm);
 }
+void write_params(hprqp_handle& h, double sigma, long long t0) { moves_and_params(h, Moves{}, sigma, t0); }
 
 // One iteration (index j of a segment of Tseg iterations; the last one is a check).
 void enqueue_iter(hprqp_handle& h, int j, int Tseg, bool trace, bool prof) {
@@ -824,14 +852,9 @@ void stage1(hprqp_handle& h) {
 }
 
 // anchor/state <- (y, w, x) buffers; exact A^T y and Q w; z/x step
+// the images of an epoch's start (its anchors ya, wa, xa are the iterate) and its first z/x step
 void reset_epoch(hprqp_handle& h) {
-  const long long n = h.n, m = h.m;
-  if (m > 0) {
-    k_copy<<<hq_grid(m, 256), 256, 0, h.st>>>(m, h.y, h.ya, nullptr);
-    launch_csr(h, h.AT, h.y, EpiStore2{h.ATy, h.ATya}, 0, no_red(h));
-  }
-  k_copy<<<hq_grid(n, 256), 256, 0, h.st>>>(n, h.w, h.wa, nullptr);
-  k_copy<<<hq_grid(n, 256), 256, 0, h.st>>>(n, h.x, h.xa, nullptr);
+  if (h.m > 0) launch_csr(h, h.AT, h.y, EpiStore2{h.ATy, h.ATya}, 0, no_red(h));
   q_apply(h, h.w, EpiStore2{h.Qw, h.Qwa}, 0, no_red(h));
   stage1(h);
 }
@@ -1273,7 +1296,7 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
     h.dflags = h.dalloc<int>(1);
     h.dprm = h.dalloc<DevParams>(1);
     HQC(hipHostMalloc((void**)&h.hs, 64 * sizeof(double), hipHostMallocDefault));
-    HQC(hipHostMalloc((void**)&h.hp, sizeof(DevParams), hipHostMallocDefault));
+    HQC(hipEventCreateWithFlags(&h.ev_done, hipEventDisableTiming));
     k_zero_ints<<<1, 64, 0, st>>>(SL_TOTAL, h.counts);
     k_zero_ints<<<1, 64, 0, st>>>(1, h.dflags);
     double** nv[] = {&h.w, &h.wa, &h.x, &h.xa, &h.ATy, &h.ATya, &h.Qw, &h.Qwa, &h.xh, &h.v, &h.q1, &h.d, &h.g,
@@ -1585,6 +1608,7 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
   long long k = 0, t = 0;
   int r = 0, term = -1, nlog = 0;
   double alpha3 = o.alpha3, R0ref = -1.0, Rr0 = -1.0, Rprev = -1.0, R = 0.0;
+  Moves start;
   if (rs) {
     // an epoch start saved by an earlier solve, already in the internal variables
     if ((m > 0 && !rs->y) || !rs->w || !rs->x) fail(HPRQP_ERR_ARG, "resume: arrays y, w, x required");
@@ -1592,17 +1616,18 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
     if (rs->restarts < 0 || !(rs->sigma > 0.0) || !std::isfinite(rs->sigma) || !(rs->alpha3 > 0.0) ||
         !std::isfinite(rs->R0ref))
       fail(HPRQP_ERR_ARG, "resume: restarts >= 0, finite sigma > 0, alpha3 > 0 and finite R0ref required");
-    if (m > 0) copy_or_zero(h, m, rs->y, h.y);
-    copy_or_zero(h, n, rs->w, h.w);
-    copy_or_zero(h, n, rs->x, h.x);
+    start.add(m, rs->y, nullptr, h.y, h.ya);
+    start.add(n, rs->w, nullptr, h.w, h.wa);
+    start.add(n, rs->x, nullptr, h.x, h.xa);
     k = rs->k; r = rs->restarts; sigma = rs->sigma; alpha3 = rs->alpha3; R0ref = rs->R0ref;
   } else {
     // a warm start in the given variables enters scaled: y/E, w/D, x/D
-    if (m > 0) copy_or_zero(h, m, y0, h.y, h.pre ? h.iEs : nullptr);
-    copy_or_zero(h, n, w0, h.w, h.pre ? h.iDs : nullptr);
-    copy_or_zero(h, n, x0, h.x, h.pre ? h.iDs : nullptr);
+    start.add(m, y0, h.pre ? h.iEs : nullptr, h.y, h.ya);
+    start.add(n, w0, h.pre ? h.iDs : nullptr, h.w, h.wa);
+    start.add(n, x0, h.pre ? h.iDs : nullptr, h.x, h.xa);
   }
-  write_params(h, sigma, 0);
+  moves_and_params(h, start, sigma, 0);
+  bool params_set = true;   // sigma and t of the next segment are on the device
   reset_epoch(h);
   // the state at the start of the current epoch (its point is the anchor ya, wa, xa)
   hprqp_state ep{k, r, 0, sigma, R0ref, alpha3, nullptr, nullptr, nullptr};
@@ -1615,7 +1640,8 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
     // around the four products (event nodes inside a replayed graph cannot be
     // read back); the other segments replay the captured graph
     const bool prof = o.profile_kernels && Tseg >= 4 && (seg++ % 4) == 1 && !(tracing && k < o.trace_iters);
-    write_params(h, sigma, t);
+    if (!params_set) write_params(h, sigma, t);
+    params_set = false;
     if (tracing && k < o.trace_iters) {
       for (int j = 0; j < Tseg; ++j) {
         enqueue_iter(h, j, Tseg, true, false);
@@ -1685,10 +1711,12 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
       }
       if (ratio <= 0.1) alpha3 = 0.2;
       // u^{r+1,0} = ubar
-      if (m > 0) k_copy<<<hq_grid(m, 256), 256, 0, h.st>>>(m, h.ybar, h.y, nullptr);
-      k_copy<<<hq_grid(n, 256), 256, 0, h.st>>>(n, h.wbar, h.w, nullptr);
-      k_copy<<<hq_grid(n, 256), 256, 0, h.st>>>(n, h.xbo, h.x, nullptr);
-      write_params(h, sigma, 0);
+      Moves re;
+      re.add(m, h.ybar, nullptr, h.y, h.ya);
+      re.add(n, h.wbar, nullptr, h.w, h.wa);
+      re.add(n, h.xbo, nullptr, h.x, h.xa);
+      moves_and_params(h, re, sigma, 0);
+      params_set = true;
       reset_epoch(h);
       t = 0;
       Rprev = -1.0;
@@ -1707,17 +1735,21 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
   }
   // output ubar of the last iteration, in the given variables when
   // preconditioned: y = E y~, z = z~ / D, w = D w~, x = D x~
-  if (m > 0) copy_or_zero(h, m, h.ybar, yo, h.pre ? h.Es : nullptr);
-  copy_or_zero(h, n, h.zbo, zo, h.pre ? h.iDs : nullptr);
-  copy_or_zero(h, n, h.wbar, wo, h.pre ? h.Ds : nullptr);
-  copy_or_zero(h, n, h.xbo, xo, h.pre ? h.Ds : nullptr);
+  Moves out;
+  out.add(m, h.ybar, h.pre ? h.Es : nullptr, yo);
+  out.add(n, h.zbo, h.pre ? h.iDs : nullptr, zo);
+  out.add(n, h.wbar, h.pre ? h.Ds : nullptr, wo);
+  out.add(n, h.xbo, h.pre ? h.Ds : nullptr, xo);
   if (sv) {
-    if (m > 0) copy_or_zero(h, m, h.ya, sv->y);
-    copy_or_zero(h, n, h.wa, sv->w);
-    copy_or_zero(h, n, h.xa, sv->x);
+    out.add(m, h.ya, nullptr, sv->y);
+    out.add(n, h.wa, nullptr, sv->w);
+    out.add(n, h.xa, nullptr, sv->x);
     ep.y = sv->y; ep.w = sv->w; ep.x = sv->x;
   }
-  HQC(hipStreamSynchronize(h.st));
+  moves_and_params(h, out, sigma, t);
+  HQC(hipEventRecord(h.ev_done, h.st));
+  if (info) enqueue_qwx(h, h.wbar, h.xbo);   // diagnostic of the shadow w_Q, after the timed solve
+  HQC(hipEventSynchronize(h.ev_done));
   if (sv) *sv = ep;
   if (info) {
     const double tsolve = now_s() - tstart;
@@ -1726,7 +1758,8 @@ void solve_impl(hprqp_handle& h, const double* y0, const double* w0, const doubl
     info->eta_p = res.eta_p; info->eta_d = res.eta_d; info->eta_gap = res.eta_gap;
     info->pobj = res.pobj; info->dobj = res.dobj; info->R_last = R;
     info->t_setup_s = h.t_setup; info->t_solve_s = tsolve; info->t_precond_s = h.t_precond;
-    info->qwx_gap = qwx_norm(h, h.wbar, h.xbo);   // diagnostic of the shadow w_Q, after the timed solve
+    HQC(hipStreamSynchronize(h.st));
+    info->qwx_gap = h.hs[SL_QWX];
   }
 }
 
