@@ -511,7 +511,7 @@ def extra_mlp(steps=20):
     f_tf, t_tf = f_fl / (f_ms * 1e-3) / 1e12, t_fl / (t_ms * 1e-3) / 1e12
     return dict(dims=list(dims), forward=dict(batch=512, gemm_ms=round(f_ms, 4), tflops=round(f_tf, 2)),
                 train_step=dict(batch=128, gemm_ms=round(t_ms, 4), tflops=round(t_tf, 2)),
-                roofline=dict(bound="mfma", kernel="k_gemm_bf16 (+ k_splitk_reduce)", achieved=round(f_tf, 2),
+                roofline=dict(bound="mfma", kernel="k_mlp_gemm", achieved=round(f_tf, 2),
                               peak=BF16_PEAK_TFLOPS, unit="TFLOP/s", frac=round(f_tf / BF16_PEAK_TFLOPS, 5),
                               traffic=None, flop_per_forward=f_fl))
 
