@@ -702,7 +702,12 @@ void enqueue_iter(hprqp_handle& h, int j, int Tseg, bool trace, bool prof) {
     if (ps >= 0) HQC(hipEventRecord(h.pev[ps][kind][edge], h.st));
   };
   // without rows the Gram Q's product carries the whole iteration (EpiQ0)
-  const bool one = h.m == 0 && h.qkind == HPRQP_Q_GRAM;
+  // (only where every thread of the last product ends with a row of its own: the
+  // row-split kernel runs an epilogue on one lane of G, and this one reads eleven
+  // vectors.  p = 7,502, q = 54,873, 74 nonzeros a row of Ahat^T: 68 us an iteration
+  // with the step in a kernel of its own, 94 in that epilogue; 5e5 rows from LDS: 206
+  // and 121)
+  const bool one = h.m == 0 && h.qkind == HPRQP_Q_GRAM && h.GT.G <= 1;
   // a3: q1 = Q xhat, v
   if (!one) {
     mark(0, 0);

@@ -194,3 +194,25 @@ def test_row_split_products_read_entries_in_pairs(lens, g):
     got = s.apply("A", x).cpu().numpy()
     s.close()
     assert np.all(np.abs(got - A @ x) <= (np.array(lens) + 1) * 2.0 ** -53 * (absA @ np.abs(x)) * 2.0)
+
+
+@pytest.mark.parametrize("lanes", [-4, -3, -2, -116, 0, 1, 2, 64])
+def test_iteration_in_either_form_for_every_product(lanes):
+    """Without rows the step after Q xhat runs in the last product's epilogue where
+    a thread there owns a row, else as a kernel of its own: the iterates of every
+    product agree (sums in another order: 1e-10 relative, as between kernels
+    elsewhere), over checks and restarts."""
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    qp = qpgen.make_lasso(seed=7, p=150, q=500)
+    dp = DeviceProblem(qp)
+    out = []
+    for g in (4, lanes):
+        s = Solver(dp, tol=0.0, max_iter=120, check_every=20, spmv_lanes=g, log_cap=20)
+        r = s.solve()
+        s.close()
+        out.append(r)
+    a, b = out
+    np.testing.assert_array_equal(a.check_log[:, [0, 1, 7]], b.check_log[:, [0, 1, 7]])
+    for k in ("x", "w", "z"):
+        u, v = getattr(a, k).cpu().numpy(), getattr(b, k).cpu().numpy()
+        assert np.max(np.abs(u - v)) <= 1e-10 * max(1.0, np.max(np.abs(u))), k
