@@ -12,12 +12,12 @@
 // only on G.
 //
 // Partial sum of one lane, entries k = b, b + G, ... < en of a row, four at a time,
-// or two where no lane of the wave has more left: the columns and values, then the
+// or as many as any lane of the wave has left: the columns and values, then the
 // gathers of a step are in flight together, also at the end of a row (clamped to
 // its last entry, the gathered value then replaced by 0), where a remainder loop
 // would wait for each in turn.  (Rows of 74 entries on 64 lanes, 5e4 of them, in
 // steps of four only have two of three loads past the end: 79 us an iteration of
-// that Lasso, 71 so.)
+// that Lasso, 70 so.)
 template <int G, int U>
 __device__ __forceinline__ double row_step(const int* __restrict__ col, const double* __restrict__ val,
                                            const double* xin, int k, int en, double sum) {
@@ -40,13 +40,11 @@ __device__ __forceinline__ double row_part(const int* __restrict__ col, const do
                                            const double* xin, int b, int en) {
   double sum = 0.0;
   for (int k = b; k < en;) {
-    if (__any(k + 2 * G < en)) {
-      sum = row_step<G, 4>(col, val, xin, k, en, sum);
-      k += 4 * G;
-    } else {
-      sum = row_step<G, 2>(col, val, xin, k, en, sum);
-      k += 2 * G;
-    }
+    if (__any(k + 3 * G < en)) sum = row_step<G, 4>(col, val, xin, k, en, sum);
+    else if (__any(k + 2 * G < en)) sum = row_step<G, 3>(col, val, xin, k, en, sum);
+    else if (__any(k + G < en)) sum = row_step<G, 2>(col, val, xin, k, en, sum);
+    else sum = row_step<G, 1>(col, val, xin, k, en, sum);
+    k += 4 * G;   // (fewer than four: nothing is left in the wave)
   }
   return sum;
 }
