@@ -39,6 +39,17 @@ struct GemmOps {
   int neg[3];   // 1: the term is subtracted
   int nt;
 };
+// Where op(B)(k, j) of a tile is, in bytes: a 64-bit base, uniform over the block, at
+// the tile's first column j0, and a 32-bit offset of the lane for column j0 + j, j < 32,
+// and k < 16.  The offset alone reaches 8 (31 ldb + 15), below 2^32 for a leading
+// dimension of up to 17 million (a factor of that order would take 2,000 TB);
+// with the columns from 0 it would reach 8 n, past 2^32 for a variable X of n >= 2^29.
+__host__ __device__ inline long long gemm_b_base(int transb, int ldb, int j0) {
+  return 8ll * (transb ? (long long)j0 : (long long)ldb * j0);
+}
+__host__ __device__ inline unsigned gemm_b_offset(int transb, unsigned ldb, unsigned j, unsigned k) {
+  return 8u * (transb ? j + ldb * k : j * ldb + k);
+}
 template <class Epi, bool PART, int WM, int WN, int NW, bool SHORT = false>
 __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int ldo, Epi epi,
                                                    const DevParams* __restrict__ prm, int jit, RedOut red, int kgroups,
@@ -83,8 +94,8 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
     // block and a byte offset that stays.  The last block of a term starts at
     // K - 16, so that it reads in range, and what the block before it has taken
     // is zeroed (K < 16: a clamped index, zeroed likewise).  Rows and columns past
-    // the edge are read from a clamped index and never stored.  (Offsets stay
-    // below 8 max(16 ld, n) bytes: square factors that fit memory, n = M N.)
+    // the edge are read from a clamped index and never stored.  (An offset into A
+    // stays below 8 (M + 12 lda) bytes: M and lda are the order of a factor.)
     struct Cur { const char *A, *B; unsigned va[WM], vb[WN]; int t, cc, nc, K; long long sa, sb; };
     struct Frag { double a[4][WM], b[4][WN]; };
     Cur lc;
@@ -96,14 +107,13 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
       const unsigned lda = pick(t, op.lda[0], op.lda[1], op.lda[2]), ldb = pick(t, op.ldb[0], op.ldb[1], op.ldb[2]);
       lc.sa = 8ll * lda; lc.sb = tb ? 8ll * ldb : 8;   // bytes per k
       lc.A = (const char*)pick(t, op.A[0], op.A[1], op.A[2]);
-      lc.B = (const char*)pick(t, op.B[0], op.B[1], op.B[2]);
+      lc.B = (const char*)pick(t, op.B[0], op.B[1], op.B[2]) + gemm_b_base(tb, ldb, j0);
 #pragma unroll
       for (int m = 0; m < WM; ++m)
         lc.va[m] = 8u * ((unsigned)min(i0 + 16 * m + li, M - 1) + (SHORT ? 0u : lda * 4u * lk));
 #pragma unroll
       for (int n = 0; n < WN; ++n) {
-        const unsigned j = min(j0 + 16 * n + li, N - 1), k = SHORT ? 0u : 4u * lk;
-        lc.vb[n] = 8u * (tb ? j + ldb * k : j * ldb + k);
+        lc.vb[n] = gemm_b_offset(tb, ldb, min(16 * n + li, N - 1 - j0), SHORT ? 0u : 4u * lk);
       }
     };
     auto load = [&](Frag& f) {

@@ -41,3 +41,18 @@ def test_split_layout_any_column_order(tmp_path):
                            os.path.join(ROOT, "tests", "native", "split_layout_check.hip"), "-o", str(exe)])
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout[-3000:]
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not installed")
+def test_gemm_addresses_up_to_the_largest_n(tmp_path):
+    """``tests/native/gemm_index_check.hip``: the operand addresses of the Kronecker
+    GEMM, from the functions that the kernel calls, against 64-bit arithmetic for
+    variables of up to 2^31 entries (32-bit offsets from the start of X wrapped at
+    2^29)."""
+    exe = tmp_path / "gemm_index_check"
+    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17",
+                           "-I", os.path.join(ROOT, "paper_2507_02470_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"),
+                           os.path.join(ROOT, "tests", "native", "gemm_index_check.hip"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout[-3000:]
