@@ -11,6 +11,17 @@
 // spreads over hundreds of waves.  No atomics; the summation order depends
 // only on G.
 //
+// Lane `lane` of a group's share of the row [b, en): entries at, at + G, ...; `left`
+// is the distance from `at` to the row's end (not positive: nothing is left).  The
+// counts are taken against the end, and positions in 64 bits: a row may end at any
+// 32-bit position, and a step past its end must not wrap.
+struct RowSpan {
+  size_t at;
+  int left;
+  __host__ __device__ RowSpan(int b, int en, int lane) : at((size_t)b + lane), left(en - b - lane) {}
+  __host__ __device__ void skip(int k) { at += k; left -= k; }
+};
+
 // Partial sum of one lane, entries k = b, b + G, ... < en of a row, four at a time,
 // or as many as any lane of the wave has left: the columns and values, then the
 // gathers of a step are in flight together, also at the end of a row (clamped to
@@ -20,31 +31,31 @@
 // that Lasso, 70 so.)
 template <int G, int U>
 __device__ __forceinline__ double row_step(const int* __restrict__ col, const double* __restrict__ val,
-                                           const double* xin, int k, int en, double sum) {
+                                           const double* xin, const RowSpan& r, double sum) {
   int c[U];
   double v[U], x[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int kk = min(k + u * G, en - 1);
+    const size_t kk = r.at + min(u * G, r.left - 1);
     c[u] = ld_stream(col + kk);
     v[u] = ld_stream(val + kk);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) x[u] = xin[c[u]];
 #pragma unroll
-  for (int u = 0; u < U; ++u) sum += v[u] * (k + u * G < en ? x[u] : 0.0);
+  for (int u = 0; u < U; ++u) sum += v[u] * (u * G < r.left ? x[u] : 0.0);
   return sum;
 }
 template <int G>
 __device__ __forceinline__ double row_part(const int* __restrict__ col, const double* __restrict__ val,
-                                           const double* xin, int b, int en) {
+                                           const double* xin, RowSpan r) {
   double sum = 0.0;
-  for (int k = b; k < en;) {
-    if (__any(k + 3 * G < en)) sum = row_step<G, 4>(col, val, xin, k, en, sum);
-    else if (__any(k + 2 * G < en)) sum = row_step<G, 3>(col, val, xin, k, en, sum);
-    else if (__any(k + G < en)) sum = row_step<G, 2>(col, val, xin, k, en, sum);
-    else sum = row_step<G, 1>(col, val, xin, k, en, sum);
-    k += 4 * G;   // (fewer than four: nothing is left in the wave)
+  while (r.left > 0) {
+    if (__any(r.left > 3 * G)) sum = row_step<G, 4>(col, val, xin, r, sum);
+    else if (__any(r.left > 2 * G)) sum = row_step<G, 3>(col, val, xin, r, sum);
+    else if (__any(r.left > G)) sum = row_step<G, 2>(col, val, xin, r, sum);
+    else sum = row_step<G, 1>(col, val, xin, r, sum);
+    r.skip(4 * G);   // (fewer than four: nothing is left in the wave)
   }
   return sum;
 }
@@ -72,7 +83,7 @@ __global__ __launch_bounds__(HQ_BLOCK) void k_csr(int nrows, const int* __restri
     if (row < nrows) {
       const int b = rowptr[row], en = rowptr[row + 1];
       if (gl == 0) ops = EpiOps<Epi>::load(e, (int)row);
-      sum = row_part<G>(col, val, xin, b + gl, en);
+      sum = row_part<G>(col, val, xin, RowSpan(b, en, gl));
     }
     if constexpr (G > 64) {
       __shared__ double wpart[HQ_BLOCK / HQ_WAVE];
@@ -231,6 +242,24 @@ __global__ void k_cols16(long long nnz, const int* __restrict__ col, unsigned sh
 }
 typedef double hq_pair __attribute__((ext_vector_type(2), aligned(8)));   // two entries' values
 
+// The entries of the row [b, en) in pairs that start at even positions, by their
+// distance `rel` (even) from the last such position at or before b: distances do not
+// wrap, wherever the row lies in the 32-bit range.
+struct RowPairs {
+  int b, en;
+  __host__ __device__ int base() const { return b & ~1; }
+  __host__ __device__ int len() const { return en - base(); }
+  // position of the pair to read: the pair at rel, clamped into the row (an empty row:
+  // to the entry before it)
+  __host__ __device__ int at(int rel) const {
+    const int last = (len() - 1) & ~1, k = base() + (rel < last ? rel : last);
+    return k > 0 ? k : 0;
+  }
+  // whether the first and the second entry of the pair at rel are the row's
+  __host__ __device__ bool first(int rel) const { return rel >= (b & 1) && rel < len(); }
+  __host__ __device__ bool second(int rel) const { return rel + 1 < len(); }
+};
+
 // Row-split kernel (G <= 64 lanes per row) gathering from an LDS copy of the input
 // vector (at most HQ_XLDS_MAX entries): for rows of tens to hundreds of nonzeros
 // over a small vector (the Lasso's Ahat^T, p columns), where the stream kernel
@@ -268,22 +297,21 @@ __global__ __launch_bounds__(HQ_XLDS_BLOCK) void k_csr_xrow(int nrows, const int
   for (int s = 0; s < (NR > 0 ? NR : 1); ++s) acc[s] = 0.0;
   for (int i = threadIdx.x; i < ncols; i += BS) xs[i] = xin[i];
   __syncthreads();
-  struct Row { int b, en; unsigned c[U / 2]; hq_pair v[U / 2]; };
+  struct Row { RowPairs p; unsigned c[U / 2]; hq_pair v[U / 2]; };
   const long long chunks = ((long long)nrows + HQ_WAVE - 1) / HQ_WAVE;
   for (long long ch = (long long)blockIdx.x * WAVES + threadIdx.x / HQ_WAVE; ch < chunks;
        ch += (long long)gridDim.x * WAVES) {   // same trip count in every lane of the wave
     const int row = (int)(ch * HQ_WAVE) + lane, rc = min(row, nrows - 1);
     const int rb = rowptr[rc], re = row < nrows ? rowptr[rc + 1] : rb;
     // the first U entries per lane of the group's row of step q, in pairs k, k + 1 of
-    // even k (clamped into the row, an empty row to the entry before it: read, never
-    // used; the last entry of an odd number of them is the second of its pair)
-    auto first = [&](const Row& r) { return (r.b & ~1) + 2 * gl; };
+    // even k (RowPairs: what is read past the row is never used; the last entry of an
+    // odd number of them is the second of its pair)
     auto fetch = [&](int q, Row& r) {
-      r.b = __shfl(rb, q * NG + gi);
-      r.en = __shfl(re, q * NG + gi);
+      r.p.b = __shfl(rb, q * NG + gi);
+      r.p.en = __shfl(re, q * NG + gi);
 #pragma unroll
       for (int u = 0; u < U / 2; ++u) {
-        const int k = max(min(first(r) + 2 * u * G, (r.en - 1) & ~1), 0);
+        const int k = r.p.at(2 * gl + 2 * u * G);
         r.c[u] = __builtin_nontemporal_load((const unsigned*)(c16 + k));
         r.v[u] = __builtin_nontemporal_load((const hq_pair*)(val + min(k, nnz - 2)));
       }
@@ -293,15 +321,19 @@ __global__ __launch_bounds__(HQ_XLDS_BLOCK) void k_csr_xrow(int nrows, const int
       double s = 0.0, x[U];
 #pragma unroll
       for (int u = 0; u < U / 2; ++u) { x[2 * u] = xs[r.c[u] & 0xffffu]; x[2 * u + 1] = xs[r.c[u] >> 16]; }
+      const int end = nnz - 1 - r.p.base();   // of the matrix's last entry
 #pragma unroll
       for (int u = 0; u < U / 2; ++u) {
-        const int k = first(r) + 2 * u * G;
-        s += (k == nnz - 1 ? r.v[u].y : r.v[u].x) * (k >= r.b && k < r.en ? x[2 * u] : 0.0);
-        s += r.v[u].y * (k + 1 < r.en ? x[2 * u + 1] : 0.0);
+        const int k = 2 * gl + 2 * u * G;
+        s += (k == end ? r.v[u].y : r.v[u].x) * (r.p.first(k) ? x[2 * u] : 0.0);
+        s += r.v[u].y * (r.p.second(k) ? x[2 * u + 1] : 0.0);
       }
-      for (int k = first(r) + U * G; k < r.en; k += 2 * G) {
-        s += ld_stream(val + k) * xs[ld_stream(c16 + k)];
-        if (k + 1 < r.en) s += ld_stream(val + k + 1) * xs[ld_stream(c16 + k + 1)];
+      const double* const vr = val + r.p.base();
+      const unsigned short* const cr = c16 + r.p.base();
+      const unsigned len = r.p.len();
+      for (unsigned k = 2 * gl + U * G; k < len; k += 2 * G) {
+        s += ld_stream(vr + k) * xs[ld_stream(cr + k)];
+        if (k + 1 < len) s += ld_stream(vr + k + 1) * xs[ld_stream(cr + k + 1)];
       }
       s = group_sum<G>(s);
       if (gl == q) mine = s;

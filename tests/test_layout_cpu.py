@@ -56,3 +56,17 @@ def test_gemm_addresses_up_to_the_largest_n(tmp_path):
                            os.path.join(ROOT, "tests", "native", "gemm_index_check.hip"), "-o", str(exe)])
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout[-3000:]
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not installed")
+def test_row_positions_up_to_the_end_of_the_32_bit_range(tmp_path):
+    """``tests/native/csr_index_check.hip``: the positions that the row-split products
+    read, for rows that end within a few steps of 2^31 entries (a step past the
+    row's end in 32 bits wrapped there)."""
+    exe = tmp_path / "csr_index_check"
+    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17",
+                           "-I", os.path.join(ROOT, "paper_2507_02470_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"),
+                           os.path.join(ROOT, "tests", "native", "csr_index_check.hip"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout[-3000:]
