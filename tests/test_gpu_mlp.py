@@ -326,3 +326,32 @@ def test_warm_start_beats_cold_start_on_held_out_family_members():
     res2 = warm_vs_cold(sur, held[:16], repeats=1)
     assert res2["fallback"] == 16
     np.testing.assert_array_equal(res2["iters_warm"], res2["iters_cold"])
+
+
+def test_more_samples_than_a_second_grid_dimension_holds():
+    """A batch of 65,538 tiles of 32 samples (blocks take a second tile of the input
+    there).  A sample's output does not depend on its batch (K = 8: one product step),
+    so every stage of the outer tiles equals that of a small batch to the last bit; with
+    an input of 0 elsewhere, the first layer's gradient is a sum over those samples
+    alone: at most that many roundings of the absolute sum, zeros add exactly."""
+    from paper_2507_02470_amd.surrogate import MLP, init_params
+    dims, B = (3, 5, 4, 2), 65_537 * 32 + 5
+    rng = np.random.default_rng(12)
+    p = init_params(dims, seed=1)
+    rows = np.concatenate([np.arange(64), np.arange(65_535 * 32, B)])   # tiles 0, 1 and the last three
+    X = np.zeros((B, 3), np.float32)
+    X[rows] = rng.standard_normal((rows.size, 3))
+    T = rng.standard_normal((B, 2)).astype(np.float32)
+    print(f"mlp batch={B}", flush=True)
+    net, small = MLP(dims, B, p), MLP(dims, rows.size, p)
+    Y, want = net.forward(X).cpu().numpy(), small.forward(X[rows]).cpu().numpy()
+    np.testing.assert_array_equal(Y[rows], want)
+    for k in ("Xs", "Z1", "A1", "Z2", "A2"):
+        np.testing.assert_array_equal(net.intermediate(k)[rows], small.intermediate(k))
+    np.testing.assert_array_equal(Y[64:65_535 * 32], np.broadcast_to(Y[64], (65_535 * 32 - 64, 2)))
+    _, g = net.loss_grad(X, T)
+    dW1 = OM.unpack(g.cpu().numpy().astype(np.float64), dims)[0]
+    Z, Xs = net.intermediate("dZ1r")[rows].astype(np.float64), net.intermediate("Xs")[rows].astype(np.float64)
+    assert np.all(np.abs(dW1 - Z.T @ Xs) <= rows.size * 2.0 ** -24 * (np.abs(Z).T @ np.abs(Xs)))
+    net.close()
+    small.close()
