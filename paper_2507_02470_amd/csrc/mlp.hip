@@ -223,18 +223,28 @@ __device__ __forceinline__ hm_f32x16 mlp_tile(const MlpJob& J, int i0, int j0, i
       b[s][q] = *reinterpret_cast<const hm_u16x8*>(Br[q] + kb);
     }
   };
+  // a lane reads what other lanes of its wave wrote, and they write again: LDS
+  // accesses keep their order across this (no instruction comes of it: a wave's
+  // LDS operations complete in order)
+  auto exchange = [&] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
   auto mul = [&](int s, int k0) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       lds[(lr + 8 * q) * 8 + (lc ^ lr)] = a[s][q];
       lds[256 + (lr + 8 * q) * 8 + (lc ^ lr)] = b[s][q];
     }
+    exchange();
     hm_u16x8 fa[4], fb[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       fa[u] = lds[li * 8 + ((2 * u + lh) ^ (li & 7))];
       fb[u] = lds[256 + li * 8 + ((2 * u + lh) ^ (li & 7))];
     }
+    exchange();
     const bool part = k0 + HM_SLAB > kend;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
