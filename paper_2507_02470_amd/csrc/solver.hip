@@ -452,7 +452,7 @@ void launch_csr_xlds(hprqp_handle& h, const Mat& M, const double* x, const Epi& 
 
 template <class Epi>
 void launch_csr_stream(hprqp_handle& h, const Mat& M, const double* x, const Epi& epi, int j, const RedOut& red) {
-  const int shape = stream_shape(M.rows, M.nnz, h.ncu), grid = hq_grid(M.rows, shape / 10);
+  const int shape = stream_shape(M.rows, M.nnz, M.maxlen, h.ncu), grid = hq_grid(M.rows, shape / 10);
   check_red_grid(grid, red);
 #define HQ_STREAM_CASE(RB, E)                                                                                     \
   case 10 * RB + E:                                                                                               \
@@ -462,9 +462,10 @@ void launch_csr_stream(hprqp_handle& h, const Mat& M, const double* x, const Epi
     HQ_STREAM_CASE(32, 2);
     HQ_STREAM_CASE(64, 2);
     HQ_STREAM_CASE(64, 4);
+    HQ_STREAM_CASE(64, 8);
     HQ_STREAM_CASE(128, 4);
-    HQ_STREAM_CASE(128, 8);
     HQ_STREAM_CASE(256, 2);
+    HQ_STREAM_CASE(256, 4);
     HQ_STREAM_CASE(256, 8);
     default: k_csr_stream<Epi, 32, 4><<<grid, HQ_BLOCK, 0, h.st>>>(M.rows, M.rp, M.ci, M.v, x, epi, h.dprm, j, red);
   }
@@ -2237,8 +2238,9 @@ void residuals_noalloc_impl(const hprqp_problem* P, const double* y, const doubl
   HQC(hipStreamSynchronize(st));
   if (hf[0] & 2) fail(HPRQP_ERR_SHAPE, "CSR structure invalid (rowptr not monotone / not ending at nnz, or column out of range)");
   if (hf[0] & 1) fail(HPRQP_ERR_BOUNDS, "invalid bounds (l > u, L > U, NaN, wrong-sided infinity) or non-finite data");
-  if (m > 0) h.A = Mat{m, n, P->a_rowptr, P->a_col, P->a_val, P->a_nnz, default_G(P->a_nnz, m, hf[1], n)};
-  if (P->qkind == HPRQP_Q_CSR) h.Q = Mat{n, n, P->q_rowptr, P->q_col, P->q_val, P->q_nnz, default_G(P->q_nnz, n, hf[2], n)};
+  if (m > 0) h.A = Mat{m, n, P->a_rowptr, P->a_col, P->a_val, P->a_nnz, default_G(P->a_nnz, m, hf[1], n), hf[1]};
+  if (P->qkind == HPRQP_Q_CSR)
+    h.Q = Mat{n, n, P->q_rowptr, P->q_col, P->q_val, P->q_nnz, default_G(P->q_nnz, n, hf[2], n), hf[2]};
   if (P->qkind == HPRQP_Q_KRON) {
     h.kp = P->kron_p; h.ks = P->kron_s; h.kB = P->kron_B; h.kC = P->kron_C; h.kS = P->kron_S; h.kT = P->kron_T;
     h.kron_mode = 1;
@@ -2246,7 +2248,7 @@ void residuals_noalloc_impl(const hprqp_problem* P, const double* y, const doubl
   if (P->qkind == HPRQP_Q_LOWRANK) { h.lr_r = P->lr_rank; h.lr_d = P->lr_d; h.lr_F = P->lr_F; }
   if (P->qkind == HPRQP_Q_GRAM)
     h.G = Mat{P->gram_p, n, P->gram_rowptr, P->gram_col, P->gram_val, P->gram_nnz,
-              default_G(P->gram_nnz, P->gram_p, hf[3], n)};
+              default_G(P->gram_nnz, P->gram_p, hf[3], n), hf[3]};
   // norms of b and c (denominators of eta_p, eta_d)
   if (m > 0) launch_elem(h, m, nullptr, EpiNormB{P->l, P->u}, 0, red_seq(h, SL_NRM, 2));
   launch_elem(h, n, nullptr, EpiNormC{P->c}, 0, red_seq(h, SL_NRM + 2, 2));

@@ -174,15 +174,38 @@ __global__ __launch_bounds__(HQ_BLOCK) void k_csr_stream(int nrows, const int* _
 }
 
 // Shape of k_csr_stream, as 10 RB + E: the most rows per block that still give every
-// CU a block and whose entries mostly fit one chunk, then the smallest chunk that
-// holds them (random rows of 5 and 10 entries, n = 2e4, m = 1e4: 4.7 us a product
-// with 32 rows, 4.4 and 6.9 with 256; larger chunks than needed cost their loads)
-inline int stream_shape(int rows, long long nnz, int ncu) {
+// CU a block and whose entries fit one chunk, with the smallest chunk that holds
+// them, since larger ones than needed cost their loads (rows of 2, 1e6 of them: 80.6 us
+// an iteration with E = 2, 81.8 with 4, 85.1 with 8; random rows of 5 and 10 entries,
+// n = 2e4, m = 1e4: 4.7 us a product with 32 rows, 4.4 and 6.9 with 256).  Entries fit
+// where the longest row says so, or with 5% to spare on the average (rows of equal
+// length need no margin: 256 rows of 8 fill a chunk of 2,048).
+// Longer rows, us an iteration:
+//  even ones, of which there are at least 1.5 blocks of 256 per CU: the stream of the
+//  matrix is what counts, 256 rows in several chunks of 2,048 (rows of 16, 18, 24 and
+//  31, n = 131,072: 19.5, 23.6, 28.5, 31.8 against 23.3, 25.7, 31.0, 36.6 with 32 rows and
+//  chunks of 1,024; n = 66,000: 13.7, 16.3, 19.8, 24.6 against 13.6, 15.1, 17.6, 21.6);
+//  uneven ones: a thread adds up a row and its block waits, so few rows a block, 64, and
+//  chunks of 2,048 for the long ones (15 on average, n = 131,072: up to 200 28.9, 32.2
+//  with 32 rows, 37.5 with 256; up to 400 38.5, 45.5, 52.0; up to 4,000 154, 168, 165).
+inline int stream_shape(int rows, long long nnz, int maxlen, int ncu) {
   const double avg = rows > 0 ? (double)nnz / rows : 0.0;
-  const int shapes[][2] = {{256, 2}, {256, 8}, {128, 4}, {128, 8}, {64, 2}, {64, 4}, {32, 2}};
-  for (const auto& s : shapes)
-    if ((long long)rows >= (long long)ncu * s[0] && 1.05 * avg * s[0] <= HQ_BLOCK * s[1]) return 10 * s[0] + s[1];
-  return 1.05 * avg * 32 <= 2 * HQ_BLOCK ? 322 : 324;
+  const bool even = maxlen >= 0 && maxlen <= 6.0 * avg;
+  const auto fits = [&](int rb, int e) {
+    return (maxlen >= 0 && (long long)maxlen * rb <= HQ_BLOCK * e) || 1.05 * avg * rb <= HQ_BLOCK * e;
+  };
+  const long long per_cu = rows / ncu;
+  if (per_cu >= 256)
+    for (int e : {2, 4, 8})
+      if (fits(256, e)) return 2560 + e;
+  if (even && per_cu >= 384) return 2568;
+  if (per_cu >= 128 && fits(128, 4)) return 1284;
+  if (per_cu >= 64) {
+    if (fits(64, 2)) return 642;
+    if (!even) return 648;
+    if (fits(64, 4)) return 644;
+  }
+  return fits(32, 2) ? 322 : 324;
 }
 
 // The stream kernel gathering from a copy of the whole input vector in LDS

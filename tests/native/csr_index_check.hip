@@ -1,4 +1,5 @@
-// Host-side check of the positions that the row-split products read (csrc/spmv.hpp):
+// Host-side check of the shape of the stream product and of the positions that the
+// row-split products read (csrc/spmv.hpp):
 // the position functions that the kernels call, stepped as the kernels step them, over
 // rows that begin and end anywhere in the 32-bit range, up to its very end.  Every
 // entry of a row is taken once, nothing outside of it is used, and what is read in
@@ -54,7 +55,48 @@ static void check_pairs(long long b, long long en, int G, long long nnz) {
   for (long long k = b; k < en; ++k) CHECK(taken[k - b] == 1, "entry %lld of [%lld, %lld) taken %d times, G %d (pairs)", k, b, en, taken[k - b], G);
 }
 
+// shape of the stream product: rows per block and entries a thread, of those built
+static void check_shapes() {
+  const int ncu = 256;
+  auto want = [&](int rows, long long nnz, int maxlen, int shape) {
+    const int got = stream_shape(rows, nnz, maxlen, ncu);
+    CHECK(got == shape, "stream_shape(%d, %lld, %d) = %d, not %d", rows, nnz, maxlen, got, shape);
+  };
+  // rows of equal length take the smallest chunk that holds them
+  want(90000, 180000, 2, 2562);      // (the assignment rows of A^T)
+  want(65536, 4 * 65536ll, 4, 2564);
+  want(65536, 8 * 65536ll, 8, 2568);
+  want(32768, 8 * 32768ll, 8, 1284);
+  want(16384, 16 * 16384ll, 16, 644);
+  want(5000, 16 * 5000ll, 16, 322);
+  // lengths that vary, or are not known, leave 5%
+  want(90000, 180000, 9, 2564);
+  want(90000, 180000, -1, 2564);
+  want(1000000, 2500000, 12, 2564);
+  // even rows of 8 to 32: many of them in several chunks of 256 rows, fewer in small blocks
+  want(98304, 98304 * 17ll, 40, 2568);
+  want(98303, 98303 * 17ll, 40, 324);
+  want(390000, 390000 * 31ll, 60, 2568);
+  want(98303, 98303 * 12ll, 30, 644);
+  // uneven ones in blocks of 64
+  want(390000, 390000 * 15ll, 90, 2568);
+  want(390000, 390000 * 15ll, 91, 648);
+  want(16384, 16384 * 15ll, 91, 648);
+  want(16383, 16383 * 15ll, 91, 322);
+  want(390000, 390000 * 17ll, -1, 648);
+  // a longest row of any size does not wrap
+  want(98303, 98303 * 12ll, 2147483647, 648);
+  for (long long rows : {0ll, 1ll, 31ll, 8191ll, 8192ll, 16384ll, 32768ll, 65535ll, 65536ll, 98304ll, 5000000ll, 67000000ll})
+    for (int avg = 0; avg <= 32; ++avg) {
+      const int shape = stream_shape((int)rows, rows * avg, -1, ncu);
+      bool built = false;
+      for (int s : {322, 324, 642, 644, 648, 1284, 2562, 2564, 2568}) built |= s == shape;
+      CHECK(built, "stream_shape(%lld, avg %d) = %d: no such kernel", rows, avg, shape);
+    }
+}
+
 int main() {
+  check_shapes();
   const long long top = (1ll << 31) - 1;
   for (int G = 1; G <= HQ_BLOCK; G *= 2)
     for (long long gap : {0ll, 1ll, 2ll, 63ll, 64ll, 255ll, 256ll, 500ll, 511ll, 512ll, 1023ll, 1024ll, 2048ll, top - 5000})

@@ -468,3 +468,30 @@ def test_row_products_at_edges_of_blocks_and_chunks(rows, avg, lanes):
     got, want = s.apply("A", x).cpu().numpy(), A @ x
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
     s.close()
+
+
+@pytest.mark.parametrize("rows,length", [(65536, 2), (65536, 3), (65537, 4), (98303, 9), (98304, 9), (98305, 20),
+                                         (100001, 32), (8192, 16), (16384, 16)])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_stream_products_of_equal_rows(rows, length, extra):
+    """The CSR-stream kernel where every row has the same length (chunks that the rows
+    of a block fill exactly, extra = 0), and one row one longer; with 256 rows
+    a block in several chunks.  Bound: a sum of k products is off by at most
+    (k + 1) u times their absolute sum."""
+    import scipy.sparse as sp
+    DP, Solver = _S()
+    rng = np.random.default_rng(rows + length)
+    cols = 3000
+    lens = np.full(rows, length)
+    lens[rows // 2] += extra
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    ci, v = rng.integers(0, cols, rp[-1]), rng.standard_normal(rp[-1])
+    print(f"stream rows={rows} length={length} extra={extra}", flush=True)
+    qp = qpgen.QP(n=cols, m=rows, qkind="zero", c=np.ones(cols), L=np.zeros(cols), U=np.ones(cols), a_rowptr=rp,
+                  a_col=ci, a_val=v, l=np.zeros(rows), u=np.ones(rows))
+    s = Solver(DP(qp), lambda_A=1.0, tol=0.0, max_iter=1, spmv_lanes=0)
+    A, absA = (sp.csr_matrix((w, ci.copy(), rp.copy()), shape=(rows, cols)) for w in (v.copy(), np.abs(v)))
+    x = rng.standard_normal(cols)
+    got = s.apply("A", x).cpu().numpy()
+    s.close()
+    assert np.all(np.abs(got - A @ x) <= (lens + 1) * 2.0 ** -53 * (absA @ np.abs(x)) * 2.0)   # both sides round
