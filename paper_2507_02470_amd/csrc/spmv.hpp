@@ -22,40 +22,44 @@ struct RowSpan {
   __host__ __device__ void skip(int k) { at += k; left -= k; }
 };
 
-// Partial sum of one lane, entries k = b, b + G, ... < en of a row, four at a time,
-// or as many as any lane of the wave has left: the columns and values, then the
-// gathers of a step are in flight together, also at the end of a row (clamped to
-// its last entry, the gathered value then replaced by 0), where a remainder loop
-// would wait for each in turn.  (Rows of 74 entries on 64 lanes, 5e4 of them, in
-// steps of four only have two of three loads past the end: 79 us an iteration of
-// that Lasso, 70 so.)
-template <int G, int U>
+// Partial sum of one lane, entries k = b, b + G, ... < en of a row, eight at a time: the
+// columns and values, then the gathers of a step are in flight together.  While every
+// lane that is left has eight, the loads are unconditional, at fixed distances from one
+// address (a clamp of each position costs more than it saves: rows of 544 on 64 lanes,
+// 7,502 of them, 28.4 us clamped, 25.6 so); then a lane loads what it has, so that the end
+// of a row is one step too (rows of 50 on 32 lanes, 4e4 of them, epilogue included:
+// 14.7 us clamped, 15.2 one entry after the other, 13.6 so; rows of 74 on 64 lanes 33.0,
+// 33.1, 31.8).  Lanes that have none left do not hold a long row up (one of 5,000 among
+// rows of 5, 4 lanes a row: 107 us, 80 and 56).
+template <int G, bool ALL>
 __device__ __forceinline__ double row_step(const int* __restrict__ col, const double* __restrict__ val,
                                            const double* xin, const RowSpan& r, double sum) {
+  constexpr int U = 8;
+  const int* const cp = col + r.at;
+  const double* const vp = val + r.at;
   int c[U];
   double v[U], x[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const size_t kk = r.at + min(u * G, r.left - 1);
-    c[u] = ld_stream(col + kk);
-    v[u] = ld_stream(val + kk);
+    c[u] = 0; v[u] = 0.0;
+    if (ALL || u * G < r.left) { c[u] = ld_stream(cp + u * G); v[u] = ld_stream(vp + u * G); }
   }
 #pragma unroll
-  for (int u = 0; u < U; ++u) x[u] = xin[c[u]];
+  for (int u = 0; u < U; ++u) {
+    x[u] = 0.0;
+    if (ALL || u * G < r.left) x[u] = xin[c[u]];
+  }
 #pragma unroll
-  for (int u = 0; u < U; ++u) sum += v[u] * (u * G < r.left ? x[u] : 0.0);
+  for (int u = 0; u < U; ++u) sum += v[u] * x[u];
   return sum;
 }
 template <int G>
 __device__ __forceinline__ double row_part(const int* __restrict__ col, const double* __restrict__ val,
                                            const double* xin, RowSpan r) {
   double sum = 0.0;
-  while (r.left > 0) {
-    if (__any(r.left > 3 * G)) sum = row_step<G, 4>(col, val, xin, r, sum);
-    else if (__any(r.left > 2 * G)) sum = row_step<G, 3>(col, val, xin, r, sum);
-    else if (__any(r.left > G)) sum = row_step<G, 2>(col, val, xin, r, sum);
-    else sum = row_step<G, 1>(col, val, xin, r, sum);
-    r.skip(4 * G);   // (fewer than four: nothing is left in the wave)
+  for (; r.left > 0; r.skip(8 * G)) {
+    if (__all(r.left > 7 * G)) sum = row_step<G, true>(col, val, xin, r, sum);
+    else sum = row_step<G, false>(col, val, xin, r, sum);
   }
   return sum;
 }

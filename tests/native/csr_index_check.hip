@@ -16,19 +16,20 @@ static long long failures = 0;
     if (!(c) && ++failures <= 20) { std::printf(__VA_ARGS__); std::printf("\n"); } \
   } while (0)
 
-// k_csr: G lanes, steps of four entries a lane
+// k_csr: G lanes, steps of eight entries a lane
 static void check_split(long long b, long long en, int G) {
   std::vector<int> taken(en - b, 0);
   for (int lane = 0; lane < G; ++lane) {
     RowSpan r((int)b, (int)en, lane);
     for (int step = 0; r.left > 0; ++step) {
       if (step > 3 + (int)((en - b) / G)) { CHECK(false, "no end: b %lld en %lld G %d", b, en, G); break; }
-      for (int u = 0; u < 4; ++u) {
-        const long long kk = (long long)(r.at + std::min(u * G, r.left - 1));
+      for (int u = 0; u < 8; ++u) {
+        if (u * G >= r.left) continue;
+        const long long kk = (long long)(r.at + u * G);
         CHECK(kk >= b && kk < en, "read %lld of [%lld, %lld) G %d", kk, b, en, G);
-        if (u * G < r.left && kk >= b && kk < en) ++taken[kk - b];
+        if (kk >= b && kk < en) ++taken[kk - b];
       }
-      r.skip(4 * G);
+      r.skip(8 * G);
     }
   }
   for (long long k = b; k < en; ++k) CHECK(taken[k - b] == 1, "entry %lld of [%lld, %lld) taken %d times, G %d", k, b, en, taken[k - b], G);
