@@ -464,6 +464,7 @@ void launch_csr_stream(hprqp_handle& h, const Mat& M, const double* x, const Epi
     HQ_STREAM_CASE(64, 4);
     HQ_STREAM_CASE(64, 8);
     HQ_STREAM_CASE(128, 4);
+    HQ_STREAM_CASE(128, 8);
     HQ_STREAM_CASE(256, 2);
     HQ_STREAM_CASE(256, 4);
     HQ_STREAM_CASE(256, 8);

@@ -184,14 +184,18 @@ __global__ __launch_bounds__(HQ_BLOCK) void k_csr_stream(int nrows, const int* _
 // n = 2e4, m = 1e4: 4.7 us a product with 32 rows, 4.4 and 6.9 with 256).  Entries fit
 // where the longest row says so, or with 5% to spare on the average (rows of equal
 // length need no margin: 256 rows of 8 fill a chunk of 2,048).
-// Longer rows, us an iteration:
-//  even ones, of which there are at least 1.5 blocks of 256 per CU: the stream of the
-//  matrix is what counts, 256 rows in several chunks of 2,048 (rows of 16, 18, 24 and
-//  31, n = 131,072: 19.5, 23.6, 28.5, 31.8 against 23.3, 25.7, 31.0, 36.6 with 32 rows and
-//  chunks of 1,024; n = 66,000: 13.7, 16.3, 19.8, 24.6 against 13.6, 15.1, 17.6, 21.6);
+// Longer rows, us an iteration of a QP with two Q products:
+//  even ones: blocks of 128 rows and chunks of 2,048 where those hold them (12 on
+//  average, n = 50,000, 90,000, 131,072, 262,144, 390,000: 22.6, 32.1, 41.2, 66.9, 95.9 against
+//  24.4, 35.6, 41.9, 64.9, 95.2 with 256 rows in several chunks and 23.9, 34.6, 44.5, 72.9, 108
+//  with 64 rows and chunks of 1,024, but 18.6 against 18.1 with those at n = 33,000), 256
+//  rows in several chunks of 2,048 for many rows,
+//  where the stream of the matrix is what counts (18 on average: 31.7, 45.7, 52.6, 84.6,
+//  124 against 30.2, 44.7, 59.5, 107, 156 with 32 rows and chunks of 1,024);
 //  uneven ones: a thread adds up a row and its block waits, so few rows a block, 64, and
-//  chunks of 2,048 for the long ones (15 on average, n = 131,072: up to 200 28.9, 32.2
-//  with 32 rows, 37.5 with 256; up to 400 38.5, 45.5, 52.0; up to 4,000 154, 168, 165).
+//  chunks of 2,048 for the long ones (15 on average, one product, n = 131,072: up to 200
+//  28.9, 32.2 with 32 rows, 37.5 with 256; up to 400 38.5, 45.5, 52.0; up to 4,000 154,
+//  168, 165).
 inline int stream_shape(int rows, long long nnz, int maxlen, int ncu) {
   const double avg = rows > 0 ? (double)nnz / rows : 0.0;
   const bool even = maxlen >= 0 && maxlen <= 6.0 * avg;
@@ -202,8 +206,10 @@ inline int stream_shape(int rows, long long nnz, int maxlen, int ncu) {
   if (per_cu >= 256)
     for (int e : {2, 4, 8})
       if (fits(256, e)) return 2560 + e;
-  if (even && per_cu >= 384) return 2568;
+  if (even && per_cu >= 768) return 2568;
   if (per_cu >= 128 && fits(128, 4)) return 1284;
+  if (even && per_cu >= 192 && fits(128, 8)) return 1288;
+  if (even && per_cu >= 384) return 2568;
   if (per_cu >= 64) {
     if (fits(64, 2)) return 642;
     if (!even) return 648;

@@ -78,7 +78,11 @@ static void check_shapes() {
   want(98304, 98304 * 17ll, 40, 2568);
   want(98303, 98303 * 17ll, 40, 324);
   want(390000, 390000 * 31ll, 60, 2568);
-  want(98303, 98303 * 12ll, 30, 644);
+  want(98303, 98303 * 12ll, 30, 1288);
+  want(49152, 49152 * 12ll, 30, 1288);
+  want(49151, 49151 * 12ll, 30, 644);
+  want(196607, 196607 * 12ll, 30, 1288);
+  want(196608, 196608 * 12ll, 30, 2568);
   // uneven ones in blocks of 64
   want(390000, 390000 * 15ll, 90, 2568);
   want(390000, 390000 * 15ll, 91, 648);
@@ -91,7 +95,7 @@ static void check_shapes() {
     for (int avg = 0; avg <= 32; ++avg) {
       const int shape = stream_shape((int)rows, rows * avg, -1, ncu);
       bool built = false;
-      for (int s : {322, 324, 642, 644, 648, 1284, 2562, 2564, 2568}) built |= s == shape;
+      for (int s : {322, 324, 642, 644, 648, 1284, 1288, 2562, 2564, 2568}) built |= s == shape;
       CHECK(built, "stream_shape(%lld, avg %d) = %d: no such kernel", rows, avg, shape);
     }
 }
