@@ -64,8 +64,11 @@ struct SmallArgs {
 
 // q_i = (M x)_i for every row, then epi(i, q_i); block reduction of the
 // epilogue's accumulators; a barrier makes the epilogue's stores visible to
-// the next phase
-template <int G, class Epi>
+// the next phase.  KEEP: the compiler may keep addresses formed from the thread index
+// from one phase to the next.  Where the registers hold them that is faster (the
+// primal methods, n = 200: 3.78 us an iteration recomputed, 3.63 kept); where they do not
+// they would be spilled.
+template <int G, bool KEEP = false, class Epi>
 __device__ __forceinline__ void small_phase(const SmallMat& M, const double* __restrict__ x, Epi e,
                                             const DevParams* __restrict__ prm, int j, const RedOut& red) {
   constexpr int NR = Epi::NR;
@@ -74,7 +77,7 @@ __device__ __forceinline__ void small_phase(const SmallMat& M, const double* __r
 #pragma unroll
   for (int s = 0; s < (NR > 0 ? NR : 1); ++s) acc[s] = 0.0;
   int tid = (int)threadIdx.x;
-  asm volatile("" : "+v"(tid));   // (no addresses kept from one phase to the next)
+  if constexpr (!KEEP) asm volatile("" : "+v"(tid));
   const int gl = tid % G, gi = tid / G;
   for (int row = gi; row < M.rows; row += HQ_SMALL_BS / G) {
     double sum = 0.0;
@@ -107,14 +110,26 @@ __device__ __forceinline__ void small_copy(T* __restrict__ dst, const T* __restr
 
 // The arrays the phases use: LDS copies when staged (copied in here), else
 // the global ones.  (Loops over the arrays are unrolled so that V and mats
-// stay in registers.)
-template <bool STAGED>
+// stay in registers.)  BATCHED: the vectors are copied eleven at a time and followed by
+// a zero, the operand of small_fast's missing entries.  Copied one by one they leave the
+// kernel with fewer scalars spilled over its phases: 3.54 us an iteration of the
+// primal methods at n = 200, 3.63 batched.
+template <bool STAGED, bool BATCHED>
 __device__ __forceinline__ void small_stage_in(const SmallArgs& a, unsigned char* lds, double* (&V)[SV_COUNT],
                                                SmallMat (&mats)[3]) {
 #pragma unroll
   for (int s = 0; s < SV_COUNT; ++s) V[s] = STAGED ? nullptr : a.vec[s];
-  if (STAGED) {
-    // the vectors, eleven at a time with their loads in flight together
+  if constexpr (STAGED && !BATCHED) {
+#pragma unroll
+    for (int s = 0; s < SV_COUNT; ++s)
+      if (a.vec[s]) {
+        double* p = (double*)(lds + a.voff[s]);
+        small_copy(p, a.vec[s], a.vlen[s]);
+        V[s] = p;
+      }
+  }
+  if constexpr (STAGED && BATCHED) {
+    // the loads of eleven vectors in flight together
     constexpr int NB = 11;
 #pragma unroll
     for (int s0 = 0; s0 < SV_COUNT; s0 += NB) {
@@ -135,6 +150,8 @@ __device__ __forceinline__ void small_stage_in(const SmallArgs& a, unsigned char
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  if (STAGED) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       SmallMat& M = mats[q];
@@ -405,7 +422,7 @@ __global__ __launch_bounds__(HQ_SMALL_BS) void k_small_segment(SmallArgs a, int 
   extern __shared__ __align__(16) unsigned char small_lds[];
   double* V[SV_COUNT];
   SmallMat mats[3] = {a.A, a.AT, a.Q};
-  small_stage_in<STAGED>(a, small_lds, V, mats);
+  small_stage_in<STAGED, true>(a, small_lds, V, mats);
   // the segment's scalars (sigma, lambda's, t0) are read by every phase: keep a copy in LDS
   SmallShared& S = small_shared();
   if (threadIdx.x == 0) {
@@ -436,7 +453,7 @@ __global__ __launch_bounds__(HQ_SMALL_BS) void k_small_primal(SmallArgs a, int T
   extern __shared__ __align__(16) unsigned char small_lds[];
   double* V[SV_COUNT];
   SmallMat mats[3] = {a.A, a.AT, a.Q};
-  small_stage_in<STAGED>(a, small_lds, V, mats);
+  small_stage_in<STAGED, false>(a, small_lds, V, mats);
   __shared__ DevParams sprm;
   if (threadIdx.x == 0) sprm = *a.prm;
   __syncthreads();
@@ -455,16 +472,16 @@ __global__ __launch_bounds__(HQ_SMALL_BS) void k_small_primal(SmallArgs a, int T
     const auto at = [&](int off) { return want_r ? rgroup + off : -1; };
     // Q x (Algorithm 6) or Q v with the v/t-step (Algorithm 7)
     if (meth == 1) {
-      small_phase<G>(Q, V[SV_X], EpiStore{V[SV_Q1]}, prm, j, none);
+      small_phase<G, true>(Q, V[SV_X], EpiStore{V[SV_Q1]}, prm, j, none);
     } else {
-      small_phase<G>(Q, V[SV_W],
+      small_phase<G, true>(Q, V[SV_W],
                      EpiP2V{V[SV_W], V[SV_X], V[SV_PTA], V[SV_PT], V[SV_WBAR], V[SV_V], V[SV_QW], V[SV_E], V[SV_PDT],
                             V[SV_PTB], want_r, check},
                      prm, j, small_red(a, at(1), at(4), check ? SL_TH + 2 : -1));
     }
     // A x with the s/y-step
     if (rows)
-      small_phase<G>(A, V[SV_X],
+      small_phase<G, true>(A, V[SV_X],
                      EpiPY{V[SV_L], V[SV_U], V[SV_YA], V[SV_Y], V[SV_YBAR], V[SV_PE], V[SV_PAX], V[SV_PDY], want_r,
                            check, store_bar},
                      prm, j, small_red(a, at(3), check ? SL_TH + 1 : -1));
@@ -472,35 +489,35 @@ __global__ __launch_bounds__(HQ_SMALL_BS) void k_small_primal(SmallArgs a, int T
     // (a value, not a reference to one of two locals: that would keep both in scratch)
     const SmallMat ATx{a.n, rows ? AT.rp : nullptr, rows ? AT.ci : nullptr, rows ? AT.v : nullptr};
     if (meth == 1) {
-      small_phase<G>(ATx, V[SV_PE],
+      small_phase<G, true>(ATx, V[SV_PE],
                      EpiP1X{V[SV_Q1], V[SV_C], V[SV_LB], V[SV_UB], V[SV_XA], V[SV_X], V[SV_XB], V[SV_ZB], V[SV_D],
                             want_r, check, store_bar, a.l1},
                      prm, j, small_red(a, at(0), check ? SL_TH : -1));
     } else {
-      small_phase<G>(ATx, V[SV_PE],
+      small_phase<G, true>(ATx, V[SV_PE],
                      EpiP2X{V[SV_V], V[SV_C], V[SV_LB], V[SV_UB], V[SV_XA], V[SV_WA], V[SV_WBAR], V[SV_PDT], V[SV_X],
                             V[SV_W], V[SV_XB], V[SV_ZB], V[SV_D], want_r, check, store_bar, a.l1},
                      prm, j, small_red(a, at(0), at(5), check ? SL_TH : -1));
     }
     if (want_r) {
       // <A dx, dy> and <dx, Q dx> (Algorithm 6) or <dv, Q dv> (Algorithm 7)
-      if (rows) small_phase<G>(A, V[SV_XB], EpiMeritA{V[SV_PAX], V[SV_PDY]}, prm, j, small_red(a, rgroup + 2));
-      if (meth == 1) small_phase<G>(Q, V[SV_XB], EpiMeritQ{V[SV_Q1], V[SV_D]}, prm, j, small_red(a, rgroup + 1));
-      else small_phase<G>(Q, V[SV_WBAR], EpiMeritQ{V[SV_QW], V[SV_E]}, prm, j, small_red(a, rgroup + 6));
+      if (rows) small_phase<G, true>(A, V[SV_XB], EpiMeritA{V[SV_PAX], V[SV_PDY]}, prm, j, small_red(a, rgroup + 2));
+      if (meth == 1) small_phase<G, true>(Q, V[SV_XB], EpiMeritQ{V[SV_Q1], V[SV_D]}, prm, j, small_red(a, rgroup + 1));
+      else small_phase<G, true>(Q, V[SV_WBAR], EpiMeritQ{V[SV_QW], V[SV_E]}, prm, j, small_red(a, rgroup + 6));
     }
     if (check) {
       // stopping quantities at (ybar, zbar, xbar): A^T ybar, A xbar, Q xbar
       if (rows) {
-        small_phase<G>(AT, V[SV_YBAR], EpiStore{V[SV_G]}, prm, j, none);
+        small_phase<G, true>(AT, V[SV_YBAR], EpiStore{V[SV_G]}, prm, j, none);
         RedOut r = none;
         for (int s = 0; s < 4; ++s) r.slot[s] = (int8_t)(SL_RA + s);
         r.active = 1;
-        small_phase<G>(A, V[SV_XB], EpiResA{V[SV_L], V[SV_U], V[SV_YBAR], V[SV_IE]}, prm, j, r);
+        small_phase<G, true>(A, V[SV_XB], EpiResA{V[SV_L], V[SV_U], V[SV_YBAR], V[SV_IE]}, prm, j, r);
       }
       RedOut r = none;
       for (int s = 0; s < 7; ++s) r.slot[s] = (int8_t)(SL_RQ + s);
       r.active = 1;
-      small_phase<G>(Q, V[SV_XB],
+      small_phase<G, true>(Q, V[SV_XB],
                      EpiResQ{V[SV_XB], V[SV_ZB], rows ? V[SV_G] : nullptr, V[SV_C], V[SV_LB], V[SV_UB], V[SV_XBO],
                              V[SV_ZBO], V[SV_ID], a.l1},
                      prm, j, r);
