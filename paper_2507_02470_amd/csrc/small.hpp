@@ -317,7 +317,7 @@ __device__ __forceinline__ void small_fast(const SmallArgs& a, double* const (&V
 }
 
 // one iteration as phases (all forms: merit, check)
-template <int G>
+template <int G, bool KEEP = false>
 __device__ __forceinline__ void small_iteration(const SmallArgs& a, double* const (&V)[SV_COUNT], const SmallMat& A,
                                                 const SmallMat& AT, const SmallMat& Q, const DevParams* prm, int j,
                                                 int Tseg) {
@@ -327,13 +327,13 @@ __device__ __forceinline__ void small_iteration(const SmallArgs& a, double* cons
   const bool want_r = rgroup >= 0;
   const bool xb_next = j >= Tseg - 2;
   // a3: q1 = Q xhat, v
-  small_phase<G>(Q, V[SV_XH], EpiQ1{V[SV_XH], V[SV_QW], V[SV_V], V[SV_Q1], 0.0}, prm, j, none);
+  small_phase<G, KEEP>(Q, V[SV_XH], EpiQ1{V[SV_XH], V[SV_QW], V[SV_V], V[SV_Q1], 0.0}, prm, j, none);
   if (a.m > 0) {
     // a4: A v, ybar, y+
-    small_phase<G>(A, V[SV_V], EpiY{V[SV_L], V[SV_U], V[SV_YA], V[SV_Y], V[SV_YBAR], want_r, check, 0.0, 0.0},
+    small_phase<G, KEEP>(A, V[SV_V], EpiY{V[SV_L], V[SV_U], V[SV_YA], V[SV_Y], V[SV_YBAR], want_r, check, 0.0, 0.0},
                    prm, j, small_red(a, want_r ? rgroup : -1, check ? SL_TH : -1));
     // a5: A^T ybar, d, A^T y+
-    small_phase<G>(AT, V[SV_YBAR], EpiAT{V[SV_ATY], V[SV_ATYA], V[SV_D], V[SV_G], V[SV_E], check, 0.0}, prm, j,
+    small_phase<G, KEEP>(AT, V[SV_YBAR], EpiAT{V[SV_ATY], V[SV_ATYA], V[SV_D], V[SV_G], V[SV_E], check, 0.0}, prm, j,
                    none);
   }
   if (check) {
@@ -341,12 +341,12 @@ __device__ __forceinline__ void small_iteration(const SmallArgs& a, double* cons
       RedOut r = none;
       for (int s = 0; s < 4; ++s) r.slot[s] = (int8_t)(SL_RA + s);
       r.active = 1;
-      small_phase<G>(A, V[SV_XB], EpiResA{V[SV_L], V[SV_U], V[SV_YBAR], V[SV_IE]}, prm, j, r);
+      small_phase<G, KEEP>(A, V[SV_XB], EpiResA{V[SV_L], V[SV_U], V[SV_YBAR], V[SV_IE]}, prm, j, r);
     }
     RedOut r = none;
     for (int s = 0; s < 7; ++s) r.slot[s] = (int8_t)(SL_RQ + s);
     r.active = 1;
-    small_phase<G>(Q, V[SV_XB],
+    small_phase<G, KEEP>(Q, V[SV_XB],
                    EpiResQ{V[SV_XB], V[SV_ZB], a.m > 0 ? V[SV_G] : nullptr, V[SV_C], V[SV_LB], V[SV_UB], V[SV_XBO],
                            V[SV_ZBO], V[SV_ID], a.l1},
                    prm, j, r);
@@ -366,8 +366,8 @@ __device__ __forceinline__ void small_iteration(const SmallArgs& a, double* cons
     for (int s = 0; s < 3; ++s) r6.slot[6 + s] = (int8_t)(SL_TH + 1 + s);
   r6.active = want_r || check;
   const SmallMat Qd{a.n, a.m > 0 ? Q.rp : nullptr, a.m > 0 ? Q.ci : nullptr, a.m > 0 ? Q.v : nullptr};
-  small_phase<G>(Qd, V[SV_D], e6, prm, j, r6);
-  if (check && a.m > 0 && Q.rp) small_phase<G>(Q, V[SV_E], EpiTheta3{V[SV_E]}, prm, j, small_red(a, SL_TH + 4));
+  small_phase<G, KEEP>(Qd, V[SV_D], e6, prm, j, r6);
+  if (check && a.m > 0 && Q.rp) small_phase<G, KEEP>(Q, V[SV_E], EpiTheta3{V[SV_E]}, prm, j, small_red(a, SL_TH + 4));
 }
 
 // The staged segment's copies of its arguments and scalars, in LDS.
@@ -417,20 +417,26 @@ __device__ __noinline__ void small_staged_iteration(int j, int Tseg) {
   small_iteration<G>(a, V, mats[0], mats[1], mats[2], &small_shared().prm, j, Tseg);
 }
 
-template <int G, bool STAGED>
+// Iterations from which a staged segment runs those between its checks from registers
+// (FAST), n G <= 1024: setting that up and its three iterations out of line take 10 us more
+// than phases inlined, an iteration from registers 2.1 us less (n = 60, segments
+// of 1, 3, 20 and 100 iterations: 30, 43, 111, 429 us in phases, 36, 54, 89, 239 so).
+// Larger staged problems have no such iterations, and are faster out of line.
+#define HQ_SMALL_FAST_FROM 8
+template <int G, bool STAGED, bool FAST = STAGED>
 __global__ __launch_bounds__(HQ_SMALL_BS) void k_small_segment(SmallArgs a, int Tseg) {
   extern __shared__ __align__(16) unsigned char small_lds[];
   double* V[SV_COUNT];
   SmallMat mats[3] = {a.A, a.AT, a.Q};
-  small_stage_in<STAGED, true>(a, small_lds, V, mats);
+  small_stage_in<STAGED, FAST>(a, small_lds, V, mats);
   // the segment's scalars (sigma, lambda's, t0) are read by every phase: keep a copy in LDS
   SmallShared& S = small_shared();
   if (threadIdx.x == 0) {
     S.prm = *a.prm;
-    if (STAGED) S.a = a;
+    if (FAST) S.a = a;
   }
   __syncthreads();
-  if constexpr (STAGED) {
+  if constexpr (FAST) {
     for (int j = 0; j < Tseg; ++j) {
       // all but the first iteration (merit) and the last two (outputs of the check)
       if (j == 1 && Tseg > 3 && (long long)max(a.n, a.m) * G <= HQ_SMALL_BS) {
@@ -440,7 +446,7 @@ __global__ __launch_bounds__(HQ_SMALL_BS) void k_small_segment(SmallArgs a, int 
       small_staged_iteration<G>(j, Tseg);
     }
   } else {
-    for (int j = 0; j < Tseg; ++j) small_iteration<G>(a, V, mats[0], mats[1], mats[2], &S.prm, j, Tseg);
+    for (int j = 0; j < Tseg; ++j) small_iteration<G, STAGED>(a, V, mats[0], mats[1], mats[2], &S.prm, j, Tseg);
   }
   small_stage_out<STAGED>(a, V);
 }

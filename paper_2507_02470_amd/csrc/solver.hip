@@ -810,7 +810,9 @@ template <int G>
 void launch_small(hprqp_handle& h, const SmallArgs& a, int Tseg) {
   const int meth = h.opt.method;
   if (meth == 0) {
-    if (a.lds_bytes > 0) k_small_segment<G, true><<<1, HQ_SMALL_BS, a.lds_bytes, h.st>>>(a, Tseg);
+    const bool fast = Tseg >= HQ_SMALL_FAST_FROM || (long long)std::max(h.n, h.m) * G > HQ_SMALL_BS;
+    if (a.lds_bytes > 0 && fast) k_small_segment<G, true><<<1, HQ_SMALL_BS, a.lds_bytes, h.st>>>(a, Tseg);
+    else if (a.lds_bytes > 0) k_small_segment<G, true, false><<<1, HQ_SMALL_BS, a.lds_bytes, h.st>>>(a, Tseg);
     else k_small_segment<G, false><<<1, HQ_SMALL_BS, 0, h.st>>>(a, Tseg);
   } else {
     if (a.lds_bytes > 0) k_small_primal<G, true><<<1, HQ_SMALL_BS, a.lds_bytes, h.st>>>(a, Tseg, meth);
@@ -822,7 +824,10 @@ void launch_small(hprqp_handle& h, const SmallArgs& a, int Tseg) {
 void small_attrs() {
   const void* ks[] = {(const void*)k_small_segment<1, true>, (const void*)k_small_segment<2, true>,
                       (const void*)k_small_segment<4, true>,  (const void*)k_small_segment<8, true>,
-                      (const void*)k_small_segment<16, true>, (const void*)k_small_primal<1, true>,
+                      (const void*)k_small_segment<16, true>,
+                      (const void*)k_small_segment<1, true, false>, (const void*)k_small_segment<2, true, false>,
+                      (const void*)k_small_segment<4, true, false>, (const void*)k_small_segment<8, true, false>,
+                      (const void*)k_small_segment<16, true, false>, (const void*)k_small_primal<1, true>,
                       (const void*)k_small_primal<2, true>,   (const void*)k_small_primal<4, true>,
                       (const void*)k_small_primal<8, true>,   (const void*)k_small_primal<16, true>};
   for (const void* k : ks) HQC(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, HQ_SMALL_LDS + 16 * SV_COUNT));

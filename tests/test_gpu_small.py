@@ -209,3 +209,26 @@ def test_iterations_between_checks_are_those_of_checked_segments(name, make):
     for o in out[1:]:
         for a, b in zip(o, out[0]):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("name,make", [("n24", lambda: qpgen.make_tiny(11, n=24, m=5)),
+                                       ("n257", lambda: _sparse(257, 100, 2)), ("n400", lambda: _sparse(400, 100, 3)),
+                                       ("m0", lambda: qpgen.make_tiny(4, n=6, m=0))])
+def test_segments_in_every_form_at_the_line_between_them(name, make):
+    """Segments of up to 7 iterations run in phases alone, from 8 on with those between
+    the checks from registers; the last segment of a solve is shorter than the others
+    and may take the other form.  Without restarts the iterates are bit-identical."""
+    DP, Solver = _S()
+    qp = make()
+    dp = DP(qp)
+    out = []
+    for T in (1, 7, 8, 9, 37):
+        s = Solver(dp, lambda_A=30.0 if qp.m else 0.0, lambda_Q=20.0, tol=0.0, max_iter=80, check_every=T,
+                   enable_restart=0, enable_sigma_update=0, small_path=1)
+        r = s.solve()
+        s.close()
+        assert r.iters == 80
+        out.append([getattr(r, k).cpu().numpy() for k in ("y", "z", "w", "x")])
+    for o in out[1:]:
+        for a, b in zip(o, out[0]):
+            np.testing.assert_array_equal(a, b)
