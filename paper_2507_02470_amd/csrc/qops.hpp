@@ -50,7 +50,12 @@ __host__ __device__ inline long long gemm_b_base(int transb, int ldb, int j0) {
 __host__ __device__ inline unsigned gemm_b_offset(int transb, unsigned ldb, unsigned j, unsigned k) {
   return 8u * (transb ? j + ldb * k : j * ldb + k);
 }
-template <class Epi, bool PART, int WM, int WN, int NW, bool SHORT = false>
+// ONE: a block per tile (kgroups 1).  In a loop over tiles the compiler forms what does
+// not change in front of it, for all three terms, and a product of a block or two of K
+// a wave is bound by the instructions up to its first load (16 x 16 tiles, us of an
+// iteration at d = 8, 128, 160, 256: 8.0, 11.5, 13.1, 15.8 in the loop, 6.7, 10.3, 11.1, 13.4
+// so; the larger tiles have more K a wave).
+template <class Epi, bool PART, int WM, int WN, int NW, bool SHORT = false, bool ONE = false>
 __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int ldo, Epi epi,
                                                    const DevParams* __restrict__ prm, int jit, RedOut red, int kgroups,
                                                    double* __restrict__ parts) {
@@ -71,21 +76,26 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
   const int per = (total + kgroups - 1) / kgroups;
   auto pick = [&](int t, auto x0, auto x1, auto x2) { return t == 0 ? x0 : t == 1 ? x1 : x2; };
   Epi e = epi;
-  e.setup(prm, jit);
+  if (!ONE) e.setup(prm, jit);
   double acc[NR > 0 ? NR : 1];
 #pragma unroll
   for (int q = 0; q < (NR > 0 ? NR : 1); ++q) acc[q] = 0.0;
-  for (int w = blockIdx.x; w < tiles * kgroups; w += gridDim.x) {
+  auto work_item = [&](int w) {
     // Work item of this block: workgroups go to the 8 XCDs in turn, so XCD x takes
     // items w = x, x + 8, ...; they are mapped to a contiguous range of an order
     // that runs through bands of HQ_GBAND tile rows column by column, and an
     // XCD's L2 then fetches a compact part of each operand.
-    const int work = tiles * kgroups, xq = work / 8, xr = work % 8, xcd = w % 8;
-    const int item = xcd * xq + min(xcd, xr) + w / 8;
-    const int tile = item % tiles, grp = item / tiles;
-    const int band = tile / (HQ_GBAND * tiles_n), in_band = tile - band * HQ_GBAND * tiles_n;
-    const int bh = min(HQ_GBAND, tiles_m - band * HQ_GBAND);
-    const int i0 = (band * HQ_GBAND + in_band % bh) * TM, j0 = (in_band / bh) * TN;
+    int i0 = 0, j0 = 0, grp = 0;
+    if (!ONE || tiles > 1) {
+      const int work = tiles * kgroups, xq = work / 8, xr = work % 8, xcd = w % 8;
+      const int item = xcd * xq + min(xcd, xr) + w / 8;
+      const int tile = ONE ? item : item % tiles;
+      grp = ONE ? 0 : item / tiles;
+      const int band = tile / (HQ_GBAND * tiles_n), in_band = tile - band * HQ_GBAND * tiles_n;
+      const int bh = min(HQ_GBAND, tiles_m - band * HQ_GBAND);
+      i0 = (band * HQ_GBAND + in_band % bh) * TM;
+      j0 = (in_band / bh) * TN;
+    }
     // this wave's K blocks, [c0, c1)
     const int g0 = min(total, grp * per), gn = min(total, g0 + per) - g0;
     const int c0 = g0 + (int)((long long)gn * wv / NW), c1 = g0 + (int)((long long)gn * (wv + 1) / NW);
@@ -166,14 +176,38 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
       if (mc + 1 < pick(mt, n0, n1, n2)) ++mc;
       else if (mt + 1 < op.nt) { ++mt; mc = 0; }
     };
-    if (c0 < c1) {
+    auto start = [&] {
       const int t0 = c0 >= n0 + n1 ? 2 : c0 >= n0 ? 1 : 0;
       mt = t0;
       mc = c0 - pick(t0, 0, n0, n0 + n1);
       load_term(mt, mc);
+    };
+    if (ONE && c1 - c0 <= 2) {
+      // a block or two without the ring, whose last loads are issued in vain and the
+      // epilogue's wait for them, and the epilogue's scalars (a memory latency and
+      // divisions) while the operands arrive
+      Frag f[2];
+      if (c1 - c0 == 2) {
+        start();
+        load(f[0]);
+        load(f[1]);
+        e.setup(prm, jit);
+        multiply(f[0]);
+        multiply(f[1]);
+      } else if (c1 - c0 == 1) {
+        start();
+        load(f[0]);
+        e.setup(prm, jit);
+        multiply(f[0]);
+      } else {
+        e.setup(prm, jit);
+      }
+    } else if (c0 < c1) {
+      start();
       Frag f[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) load(f[r]);
+      if (ONE) e.setup(prm, jit);
       int c = c0;
       for (; c + R <= c1; c += R) {   // no conditional load: the waits count exactly the loads they need
 #pragma unroll
@@ -231,8 +265,11 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
         }
       }
     }
-    __syncthreads();   // tile_w is rewritten by the next tile
-  }
+    if constexpr (!ONE) __syncthreads();   // tile_w is rewritten by the next tile
+  };
+  if constexpr (ONE) work_item(blockIdx.x);
+  else
+    for (int w = blockIdx.x; w < tiles * kgroups; w += gridDim.x) work_item(w);
   if constexpr (!PART) {
     if (red.active) block_reduce_store<NR, Epi::MAXMASK>(acc, red);
   }

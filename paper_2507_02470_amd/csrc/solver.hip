@@ -576,9 +576,16 @@ void launch_gemm_tile(hprqp_handle& h, int M, int N, const GemmOps& ops, const E
   const int tiles = tile_count(M, N, 16 * WM, 16 * WN);
   const int G = h.kron_groups;
   if (G <= 1) {
-    check_red_grid(std::min(tiles, HQ_GRID_CAP), red);
-    k_dgemm<Epi, false, WM, WN, NW, SHORT><<<std::min(tiles, HQ_GRID_CAP), 64 * NW, 0, h.st>>>(
-        M, N, ops, M, epi, h.dprm, j, red, 1, nullptr);
+    const int grid = std::min(tiles, HQ_GRID_CAP);
+    check_red_grid(grid, red);
+    if constexpr (WM * WN == 1) {
+      if (tiles == grid) {
+        k_dgemm<Epi, false, WM, WN, NW, SHORT, true><<<grid, 64 * NW, 0, h.st>>>(M, N, ops, M, epi, h.dprm, j, red, 1,
+                                                                               nullptr);
+        return;
+      }
+    }
+    k_dgemm<Epi, false, WM, WN, NW, SHORT><<<grid, 64 * NW, 0, h.st>>>(M, N, ops, M, epi, h.dprm, j, red, 1, nullptr);
   } else {
     k_dgemm<EpiStore, true, WM, WN, NW, SHORT><<<std::min(tiles * G, HQ_GRID_CAP), 64 * NW, 0, h.st>>>(
         M, N, ops, M, EpiStore{nullptr}, h.dprm, j, no_red(h), G, h.kparts);

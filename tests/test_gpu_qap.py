@@ -186,3 +186,29 @@ def test_invalid_kron_kernel_is_rejected():
     qp = qpgen.make_qap(seed=1, d=6)
     with pytest.raises(HPRQPError):
         Solver(DP(qp), lambda_A=1.0, lambda_Q=1.0, kron_kernel=3)
+
+
+@pytest.mark.parametrize("s,p,terms", [(4, 4, 0), (15, 16, 0), (16, 16, 0), (128, 129, 0), (129, 128, 0), (256, 256, 0),
+                                       (257, 240, 0), (60, 61, 3), (16, 5000, 0), (1030, 1024, 0)])
+def test_kron_products_of_few_blocks_a_wave(s, p, terms):
+    """16 x 16 tiles (kron_kernel = 0): one tile alone, no, one, two and more blocks of K a
+    wave, one block per tile and, past 4,096 tiles, several tiles a block.  Bound as
+    for test_kron_tiles."""
+    DP, Solver = _S()
+    rng = np.random.default_rng(s + p)
+    B, T = rng.standard_normal((2, p, p))
+    C, S = rng.standard_normal((2, s, s))
+    extra = dict(kron_S=S, kron_T=T) if terms else {}
+    qp = qpgen.QP(n=s * p, m=0, qkind="kron", c=np.zeros(s * p), L=np.full(s * p, -1.0), U=np.ones(s * p),
+                  a_rowptr=np.zeros(1, dtype=np.int32), a_col=np.zeros(0, dtype=np.int32), a_val=np.zeros(0),
+                  l=np.zeros(0), u=np.zeros(0), kron_B=B, kron_C=C, **extra)
+    print(f"kron few s={s} p={p} terms={terms}", flush=True)
+    h = Solver(DP(qp), lambda_A=1.0, lambda_Q=1.0, tol=0.0, max_iter=1, kron_kernel=0)
+    X = rng.standard_normal((s, p))
+    got = h.apply("Q", X.ravel(order="F")).cpu().numpy().reshape((s, p), order="F")
+    h.close()
+    want, size = C @ X @ B.T, np.abs(C) @ np.abs(X) @ np.abs(B.T)
+    if terms:
+        want = want - X @ T.T - S @ X
+        size = size + np.abs(X) @ np.abs(T.T) + np.abs(S) @ np.abs(X)
+    assert np.all(np.abs(got - want) <= 2 * (2 * s + 2 * p + 16) * 2.0 ** -53 * size)   # both sides round
