@@ -207,8 +207,9 @@ void hprqp_default_options(hprqp_options *opt);
  * product is deterministic), runs the power method when lambda_A/lambda_Q
  * are not given (Section 4.1), computes sigma0 and allocates the workspace
  * (about 34 n + 15 m doubles plus A^T, plus a reordered copy of each matrix
- * whose product runs on the panel-ordered or column-split layout, and the
- * latter's per-panel partial sums).  The problem arrays are borrowed.
+ * whose product runs on the panel-ordered or column-split layout, the latter's
+ * per-panel partial sums, and 16-bit columns, 2 bytes an entry, of one whose
+ * row-split product gathers from LDS).  The problem arrays are borrowed.
  * Returns HPRQP_ERR_BOUNDS / HPRQP_ERR_SHAPE on invalid data. */
 hprqp_status hprqp_create(const hprqp_problem *prob, const hprqp_options *opt,
                           hipStream_t stream, hprqp_handle **out);
@@ -344,7 +345,10 @@ void hprqp_destroy(hprqp_handle *h);
  * counts from the start of hprqp_solve_batch, and an instance still running
  * then stops at its next check with HPRQP_TIME_LIMIT (0: no limit).
  * Instances are scheduled largest first (hprqp_batch_set_priority sets
- * another order). */
+ * another order).  Device memory: 16 bytes per nonzero of each distinct A (its
+ * transpose, with the rows' positions in A), 80 or 128 bytes per row of each
+ * distinct F (lr_rank up to 10 or 16), and 40 bytes per entry of the largest
+ * instance of a kernel and workgroup resident at once. */
 hprqp_status hprqp_batch_create(int32_t count, const hprqp_problem *probs,
                                 const hprqp_options *opt, hipStream_t stream, hprqp_batch **out);
 

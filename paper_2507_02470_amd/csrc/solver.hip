@@ -323,6 +323,12 @@ struct hprqp_handle {
     owned.push_back(p);
     return (T*)p;
   }
+  void dfree(const void* p) {   // one of dalloc's, before the handle's end
+    const auto it = std::find(owned.begin(), owned.end(), p);
+    if (it == owned.end()) return;
+    HQC(hipFree(*it));
+    owned.erase(it);
+  }
   ~hprqp_handle() {
     if (gexec) hipGraphExecDestroy(gexec);
     if (graph) hipGraphDestroy(graph);
@@ -1533,6 +1539,12 @@ void create_impl(const hprqp_problem* P, const hprqp_options* opt, hipStream_t s
     } else if (opt->spmv_lanes != -1) {
       fail(HPRQP_ERR_ARG, "spmv_lanes must be -4, -3, -2, -1, 0, a power of 2 <= 256 or -100 - g (g <= 64)");
     }
+    // 16-bit columns of a product that was timed, or chosen at first, and is not taken
+    for (Mat* M : {&h.A, &h.AT, &h.Q, &h.G, &h.GT})
+      if (M->c16 && !is_xrow(M->G) && !is_xrow(M->G_np)) {
+        h.dfree(M->c16);
+        M->c16 = nullptr;
+      }
     // the operators as given (hprqp_apply, and the residuals of a preconditioned
     // handle) take the kernel chosen for the method's copy: the same arrays
     // without preconditioning; with it the unscaled arrays have the same

@@ -216,3 +216,29 @@ def test_iteration_in_either_form_for_every_product(lanes):
     for k in ("x", "w", "z"):
         u, v = getattr(a, k).cpu().numpy(), getattr(b, k).cpu().numpy()
         assert np.max(np.abs(u - v)) <= 1e-10 * max(1.0, np.max(np.abs(u))), k
+
+
+def test_columns_of_a_product_not_taken_are_given_back():
+    """Autotuning times the row-split product over LDS, which reads 16-bit columns of its
+    own: a handle that then runs another product holds no more memory than one
+    that never timed it (each copy would be 24 MB here)."""
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    rng = np.random.default_rng(3)
+    m, n, per = 12_000, 12_000, 1000
+    rp = per * np.arange(m + 1)
+    qp = qpgen.QP(n=n, m=m, qkind="zero", c=np.ones(n), L=np.zeros(n), U=np.ones(n), a_rowptr=rp,
+                  a_col=rng.integers(0, n, rp[-1]), a_val=rng.standard_normal(rp[-1]), l=np.zeros(m), u=np.ones(m))
+    dp = DeviceProblem(qp)
+    used = []
+    for tune in (0, 1, 0, 1):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        s = Solver(dp, lambda_A=1.0, tol=0.0, max_iter=1, spmv_lanes=8, spmv_autotune=tune)
+        torch.cuda.synchronize()
+        used.append(free - torch.cuda.mem_get_info()[0])
+        x = rng.standard_normal(n)
+        y = s.apply("A", x)
+        s.close()
+    print("handle bytes", used, flush=True)
+    assert bool(torch.isfinite(y).all())
+    assert abs(used[3] - used[2]) < 12_000_000
