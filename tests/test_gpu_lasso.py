@@ -242,3 +242,30 @@ def test_columns_of_a_product_not_taken_are_given_back():
     print("handle bytes", used, flush=True)
     assert bool(torch.isfinite(y).all())
     assert abs(used[3] - used[2]) < 12_000_000
+
+
+@pytest.mark.parametrize("p,q,per_row", [(15_000, 700, 12), (15_000, 300, 200), (40_000, 64, 64)])
+@pytest.mark.parametrize("m0_form", [-4, -3])
+def test_iteration_in_the_epilogue_of_a_layout(p, q, per_row, m0_form):
+    """As test_iteration_in_either_form_for_every_product, with an Ahat^T that has a
+    column-split layout (more than 14,336 columns; panels of 16,384 and of 2,048) and a
+    panel-ordered one: the iteration in the epilogue of those products."""
+    from paper_2507_02470_amd.solver import DeviceProblem, Solver
+    rng = np.random.default_rng(p + q)
+    rp = per_row * np.arange(p + 1)
+    ci = np.argsort(rng.random((p, q)), axis=1)[:, :per_row].ravel()
+    v = rng.standard_normal(rp[-1]) / np.sqrt(p * per_row / q)
+    none = dict(a_rowptr=np.zeros(1, np.int32), a_col=np.zeros(0, np.int32), a_val=np.zeros(0), l=np.zeros(0), u=np.zeros(0))
+    qp = qpgen.QP(n=q, m=0, qkind="gram", c=rng.standard_normal(q), L=np.full(q, -np.inf), U=np.full(q, np.inf),
+                  gram_p=p, gram_rowptr=rp, gram_col=ci, gram_val=v, l1_weight=0.1, **none)
+    dp = DeviceProblem(qp)
+    out = []
+    for g in (4, m0_form):
+        s = Solver(dp, tol=0.0, max_iter=120, check_every=20, spmv_lanes=g, log_cap=20)
+        out.append(s.solve())
+        s.close()
+    a, b = out
+    np.testing.assert_array_equal(a.check_log[:, [0, 1, 7]], b.check_log[:, [0, 1, 7]])
+    for k in ("x", "w", "z"):
+        u, w = getattr(a, k).cpu().numpy(), getattr(b, k).cpu().numpy()
+        assert np.max(np.abs(u - w)) <= 1e-10 * max(1.0, np.max(np.abs(u))), k
