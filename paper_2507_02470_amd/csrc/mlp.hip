@@ -711,15 +711,15 @@ int eg(long long work) {
   return (int)std::max(1LL, std::min(g, 4096LL));
 }
 
-// K splits of a GEMM: doubled while the launch holds fewer than 4 waves per
-// CU, each split keeps at least 4 k-steps of 16 and the partial products stay
-// below 32 Ki floats per CU (the network's GEMMs are small: a 512 x 512 output
-// is 64 tiles of 64 x 64, 256 waves, too few to hide the fragment loads on 256 CUs)
+// K splits of a network GEMM, waves of the block that has the tile: doubled while the
+// launch holds fewer than 4 waves per CU (a wave per 32 x 32 tile and split, counted in
+// fours) and each split keeps at least 4 k-steps of 16.  The network's GEMMs are small: a
+// 512 x 512 output is 256 tiles, a wave a CU, too few to hide the operand loads.
 int gemm_splits(int M, int N, int K, int ncu) {
-  const long long waves = 4LL * ((M + 63) / 64) * ((N + 63) / 64), most = 2LL * ncu * 4096 * 4;
+  const long long waves = 4LL * ((M + 63) / 64) * ((N + 63) / 64);
   const int ksteps = (K + 15) / 16;
   int S = 1;
-  while (S < 8 && waves * S < 4LL * ncu && ksteps >= 8 * S && (long long)(2 * S) * M * N <= most) S *= 2;
+  while (S < 8 && waves * S < 4LL * ncu && ksteps >= 8 * S) S *= 2;
   return S;
 }
 

@@ -876,8 +876,8 @@ void stage1(hprqp_handle& h) {
               no_red(h));
 }
 
-// anchor/state <- (y, w, x) buffers; exact A^T y and Q w; z/x step
-// the images of an epoch's start (its anchors ya, wa, xa are the iterate) and its first z/x step
+// The images A^T y and Q w of an epoch's start, taken exactly, and its first z/x step.  The
+// anchors ya, wa, xa must already equal y, w, x (the Moves of a start or a restart).
 void reset_epoch(hprqp_handle& h) {
   if (h.m > 0) launch_csr(h, h.AT, h.y, EpiStore2{h.ATy, h.ATya}, 0, no_red(h));
   q_apply(h, h.w, EpiStore2{h.Qw, h.Qwa}, 0, no_red(h));
@@ -1240,10 +1240,9 @@ void autotune_heavy_q(hprqp_handle& h) {
 }
 
 // Lanes per row of the row-split kernel, or 0 for the CSR-stream kernel
-// (short rows: average up to 32 nonzeros and none longer than 4096).  The
-// variant gathering from an LDS copy of the vector is left to the autotuner:
-// measured on a 5e7-nonzero A^T with an 80 KB vector it was slower (322 us vs
-// 262 us) than gathering through the L2.
+// (short rows: average up to 32 nonzeros and none longer than 4096).  Where the
+// row-split kernel gathers from an LDS copy of the vector instead, create's choice
+// says; the stream kernel's variant of that is left to the autotuner.
 int default_G(long long nnz, int rows, int maxlen, int cols) {
   const double avg = rows > 0 ? (double)nnz / rows : 1.0;
   (void)cols;
