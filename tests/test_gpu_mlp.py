@@ -355,3 +355,29 @@ def test_more_samples_than_a_second_grid_dimension_holds():
     assert np.all(np.abs(dW1 - Z.T @ Xs) <= rows.size * 2.0 ** -24 * (np.abs(Z).T @ np.abs(Xs)))
     net.close()
     small.close()
+
+
+@pytest.mark.parametrize("rows,m,score", [(5, 3, True), (16, 3, True), (37, 3, False), (37, 0, True)])
+def test_starts_in_chunks_are_those_of_single_calls(rows, m, score):
+    """The starts of more samples than the network's batch are written chunk by chunk
+    into one set of arrays: equal, to the last bit, to a call per chunk, for less than
+    a chunk, exactly one, a ragged last one, no rows of A and no length output."""
+    from paper_2507_02470_amd.surrogate import WarmStartSurrogate
+    rng = np.random.default_rng(rows)
+    n = 9
+    base = qpgen.QP(n=n, m=m, qkind="lowrank", c=np.zeros(n), L=np.zeros(n), U=np.full(n, 0.05),
+                    a_rowptr=np.zeros(m + 1, np.int32), a_col=np.zeros(0, np.int32), a_val=np.zeros(0),
+                    l=np.zeros(m), u=np.zeros(m), lr_d=np.ones(n), lr_F=np.zeros((n, 2)))
+    sur = WarmStartSurrogate(base, hidden=16, max_batch=16, seed=2, predict_length=score)
+    X = rng.standard_normal((rows, n + m)).astype(np.float32)
+    X[rows // 2, 0] = np.inf                       # a sample that starts from the origin
+    got = sur.starts(X)
+    parts = [sur.net.warm_start(X[b:b + 16], n, m, base.L, base.U) for b in range(0, rows, 16)]
+    for k, name in enumerate(("y0", "w0", "x0", "bad", "score")):
+        if got[k] is None:
+            assert name == "score" and not score and all(p[k] is None for p in parts)
+            continue
+        want = torch.cat([p[k] for p in parts])
+        assert got[k].shape == want.shape and torch.equal(got[k].nan_to_num(7.0), want.nan_to_num(7.0)), name
+    assert got[3][rows // 2] == 1
+    sur.net.close()
