@@ -91,6 +91,13 @@ hprqp_status hprqp_mlp_warm_start(hprqp_mlp *net, int32_t batch, const float *X,
                                   const double *L, const double *U, double *y0, double *w0, double *x0,
                                   int32_t *bad, float *score);
 
+/* The same for any number of members (count > 0; the arrays hold count rows):
+ * the network runs on max_batch of them at a time, with one wait at the end.
+ * hprqp_mlp_gemm_stats and the stages then describe the last of those runs. */
+hprqp_status hprqp_mlp_warm_starts(hprqp_mlp *net, int32_t count, const float *X, int32_t n, int32_t m,
+                                   const double *L, const double *U, double *y0, double *w0, double *x0,
+                                   int32_t *bad, float *score);
+
 /* One Adam step (bias-corrected) on the FP32 master parameters with the
  * last gradient; refreshes the BF16 weight copies. */
 hprqp_status hprqp_mlp_adam(hprqp_mlp *net, float lr, float beta1, float beta2, float eps);

@@ -909,6 +909,30 @@ int forward_impl(hprqp_mlp& n, int B, const float* X, const MlpOut& out) {
   return parts;
 }
 
+// Warm starts of `count` samples in chunks of the network's batch: every chunk's
+// launches are queued behind the last one's (they share its buffers, in the order of
+// the stream), one wait at the end.  With a wait a chunk, 2,048 samples in chunks of
+// 256 took 0.46 ms; with one, 0.33 ms.
+void warm_impl(hprqp_mlp* n, int count, int most, const float* X, int qn, int qm, const double* L, const double* U,
+               double* y0, double* w0, double* x0, int32_t* bad, float* score) {
+  if (!n || !L || !U || !w0 || !x0 || !bad || (qm > 0 && !y0)) mfail(HPRQP_ERR_ARG, "NULL argument");
+  if (qn <= 0 || qm < 0 || (qm + 2 * qn != n->d[3] && qm + 2 * qn + 1 != n->d[3]))
+    mfail(HPRQP_ERR_SHAPE, "n_out must equal m + 2 n or m + 2 n + 1");
+  if (score && qm + 2 * qn + 1 != n->d[3]) mfail(HPRQP_ERR_SHAPE, "score needs n_out = m + 2 n + 1");
+  if (count <= 0 || count > most || !X) mfail(HPRQP_ERR_ARG, "batch out of range or NULL input");
+  for (long long s = 0; s < count; s += n->maxb) {
+    const int B = (int)std::min<long long>(n->maxb, count - s);
+    MlpOut out;
+    out.L = L; out.U = U; out.n = qn; out.m = qm;
+    out.y0 = y0 ? y0 + s * qm : nullptr; out.w0 = w0 + s * qn; out.x0 = x0 + s * qn;
+    out.bad = bad + s; out.score = score ? score + s : nullptr;
+    forward_impl(*n, B, X + s * n->d[0], out);
+    k_warm_fix<<<B, 256, 0, n->st>>>(qn, qm, out.bad, out.y0, out.w0, out.x0);
+  }
+  HMC(hipGetLastError());
+  HMC(hipStreamSynchronize(n->st));
+}
+
 void loss_grad_impl(hprqp_mlp& n, int B, const float* X, const float* T, const float* w, float* loss_host,
                     float* grad) {
   if (!T) mfail(HPRQP_ERR_ARG, "NULL targets");
@@ -1037,18 +1061,12 @@ hprqp_status hprqp_mlp_set_scaling(hprqp_mlp* n, const float* in_mean, const flo
 
 hprqp_status hprqp_mlp_warm_start(hprqp_mlp* n, int32_t batch, const float* X, int32_t qn, int32_t qm, const double* L,
                                   const double* U, double* y0, double* w0, double* x0, int32_t* bad, float* score) {
-  HM_GUARD(
-      if (!n || !L || !U || !w0 || !x0 || !bad || (qm > 0 && !y0)) mfail(HPRQP_ERR_ARG, "NULL argument");
-      if (qn <= 0 || qm < 0 || (qm + 2 * qn != n->d[3] && qm + 2 * qn + 1 != n->d[3]))
-        mfail(HPRQP_ERR_SHAPE, "n_out must equal m + 2 n or m + 2 n + 1");
-      if (score && qm + 2 * qn + 1 != n->d[3]) mfail(HPRQP_ERR_SHAPE, "score needs n_out = m + 2 n + 1");
-      MlpOut out;
-      out.L = L; out.U = U; out.y0 = y0; out.w0 = w0; out.x0 = x0; out.bad = bad; out.score = score;
-      out.n = qn; out.m = qm;
-      forward_impl(*n, batch, X, out);
-      k_warm_fix<<<batch, 256, 0, n->st>>>(qn, qm, bad, y0, w0, x0);
-      HMC(hipGetLastError());
-      HMC(hipStreamSynchronize(n->st)));
+  HM_GUARD(warm_impl(n, batch, n ? n->maxb : 0, X, qn, qm, L, U, y0, w0, x0, bad, score));
+}
+
+hprqp_status hprqp_mlp_warm_starts(hprqp_mlp* n, int32_t count, const float* X, int32_t qn, int32_t qm, const double* L,
+                                   const double* U, double* y0, double* w0, double* x0, int32_t* bad, float* score) {
+  HM_GUARD(warm_impl(n, count, INT32_MAX, X, qn, qm, L, U, y0, w0, x0, bad, score));
 }
 
 hprqp_status hprqp_mlp_fit_scaling(hprqp_mlp* n, int64_t rows, const float* X, const float* T, float* stats_host) {

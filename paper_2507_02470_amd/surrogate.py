@@ -35,8 +35,8 @@ def _load():
         lib.hprqp_mlp_get_params.argtypes = [_vp, C.POINTER(C.c_float)]
         lib.hprqp_mlp_set_params.argtypes = [_vp, C.POINTER(C.c_float)]
         lib.hprqp_mlp_set_scaling.argtypes = [_vp] + [C.POINTER(C.c_float)] * 4
-        lib.hprqp_mlp_warm_start.argtypes = [_vp, C.c_int32, _vp, C.c_int32, C.c_int32, _vp, _vp, _vp, _vp, _vp, _vp,
-                                             _vp]
+        lib.hprqp_mlp_warm_start.argtypes = lib.hprqp_mlp_warm_starts.argtypes = [
+            _vp, C.c_int32, _vp, C.c_int32, C.c_int32, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
         lib.hprqp_mlp_gemm_stats.argtypes = [_vp, C.POINTER(C.c_double), C.POINTER(C.c_double)]
         lib.hprqp_mlp_fit_scaling.argtypes = [_vp, C.c_int64, _vp, _vp, C.POINTER(C.c_float)]
         lib.hprqp_mlp_intermediate.argtypes = [_vp, C.c_int32, _vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
@@ -48,8 +48,8 @@ def _load():
                                         C.c_int64, _vp, C.c_int64, C.c_int32, C.c_int32, _vp, _vp]
         for f in ("hprqp_mlp_create", "hprqp_mlp_forward", "hprqp_mlp_loss_grad", "hprqp_mlp_adam",
                   "hprqp_mlp_get_params", "hprqp_mlp_set_params", "hprqp_mlp_set_scaling", "hprqp_mlp_warm_start",
-                  "hprqp_mlp_gemm_stats", "hprqp_gemm_bf16", "hprqp_mlp_fit_scaling", "hprqp_mlp_intermediate", "hprqp_family_features",
-                  "hprqp_family_targets"):
+                  "hprqp_mlp_warm_starts", "hprqp_mlp_gemm_stats", "hprqp_gemm_bf16", "hprqp_mlp_fit_scaling",
+                  "hprqp_mlp_intermediate", "hprqp_family_features", "hprqp_family_targets"):
             getattr(lib, f).restype = C.c_int
         lib._mlp_ready = True
     return lib
@@ -163,23 +163,22 @@ class MLP:
         """(y0, w0, x0, bad, score): the FP64 start, the flags of samples
         started from the origin, and the predicted log iteration count of each
         solve (None unless the network has that output column)."""
+        return self._warm(self.lib.hprqp_mlp_warm_start, X, n, m, L, U)
+
+    def warm_starts(self, X, n, m, L, U):
+        """warm_start of any number of samples: chunks of max_batch, one wait."""
+        return self._warm(self.lib.hprqp_mlp_warm_starts, X, n, m, L, U)
+
+    def _warm(self, call, X, n, m, L, U):
         X = self._f32(X)
-        out = self._start_arrays(X.shape[0], n, m)
+        B = X.shape[0]
         f64 = dict(dtype=torch.float64, device=self.device)
-        self._warm_start(X, n, m, torch.as_tensor(L, **f64).contiguous(), torch.as_tensor(U, **f64).contiguous(), *out)
-        return (out[0][:, :m], *out[1:])
-
-    def _start_arrays(self, rows, n, m):
-        f64 = dict(dtype=torch.float64, device=self.device)
-        y0 = torch.empty((rows, max(m, 1)), **f64); w0 = torch.empty((rows, n), **f64); x0 = torch.empty((rows, n), **f64)
-        bad = torch.empty(rows, dtype=torch.int32, device=self.device)
-        score = torch.empty(rows, dtype=torch.float32, device=self.device) if self.dims[3] == m + 2 * n + 1 else None
-        return y0, w0, x0, bad, score
-
-    def _warm_start(self, X, n, m, L, U, y0, w0, x0, bad, score):
-        """The library's call on contiguous device arrays of X.shape[0] rows."""
-        N.check(self.lib.hprqp_mlp_warm_start(self.h, X.shape[0], _p(X), n, m, _p(L), _p(U), _p(y0), _p(w0), _p(x0),
-                                              _p(bad), _p(score)))
+        y0 = torch.empty((B, max(m, 1)), **f64); w0 = torch.empty((B, n), **f64); x0 = torch.empty((B, n), **f64)
+        bad = torch.empty(B, dtype=torch.int32, device=self.device)
+        score = torch.empty(B, dtype=torch.float32, device=self.device) if self.dims[3] == m + 2 * n + 1 else None
+        Lt = torch.as_tensor(L, **f64).contiguous(); Ut = torch.as_tensor(U, **f64).contiguous()
+        N.check(call(self.h, B, _p(X), n, m, _p(Lt), _p(Ut), _p(y0), _p(w0), _p(x0), _p(bad), _p(score)))
+        return y0[:, :m], w0, x0, bad, score
 
     def gemm_stats(self):
         ms, fl = C.c_double(), C.c_double()
@@ -300,20 +299,7 @@ class WarmStartSurrogate:
     def starts(self, X):
         """Warm starts (y0, w0, x0, bad, score) for the rows of X, in chunks of
         the network's max batch (score: None without the length output)."""
-        X = torch.as_tensor(X, dtype=torch.float32, device=self.device).contiguous()
-        if X.shape[0] == 0:
-            raise RuntimeError("no samples")
-        # one set of arrays, each chunk into its rows of them, and the box taken to the
-        # device once: an allocation and a copy of each per chunk, joined at the end, took
-        # 0.80 ms for 2,048 members in chunks of 256, half of what their warm start saves
-        f64 = dict(dtype=torch.float64, device=self.device)
-        L = torch.as_tensor(self.base.L, **f64).contiguous()
-        U = torch.as_tensor(self.base.U, **f64).contiguous()
-        out = self.net._start_arrays(X.shape[0], self.n, self.m)
-        for b0 in range(0, X.shape[0], self.net.max_batch):
-            rows = slice(b0, b0 + self.net.max_batch)
-            self.net._warm_start(X[rows], self.n, self.m, L, U, *(None if t is None else t[rows] for t in out))
-        return (out[0][:, :self.m], *out[1:])
+        return self.net.warm_starts(X, self.n, self.m, self.base.L, self.base.U)
 
 
 def warm_vs_cold(sur: WarmStartSurrogate, samples, tol=1e-8, max_iter=200_000, repeats=3, order=True):
@@ -343,12 +329,11 @@ def warm_vs_cold(sur: WarmStartSurrogate, samples, tol=1e-8, max_iter=200_000, r
         rw = bs.solve(y0=y0.reshape(-1), w0=w0.reshape(-1), x0=x0.reshape(-1), split=False)
         bs.close()
         failed = [i for i, f in enumerate(rw.infos) if f["term"] != "solved"]
-        fallback = sorted(set(failed) | set(np.nonzero(bad.cpu().numpy())[0].tolist()))
-        kw = rw.kernel_s
         rf = solve_family(base, [samples[i] for i in failed], tol=tol, max_iter=max_iter) if failed else None
         torch.cuda.synchronize()
         t_warm.append(time.perf_counter() - t0)
-        k_warm.append(kw + (rf.kernel_s if failed else 0.0))
+        k_warm.append(rw.kernel_s + (rf.kernel_s if failed else 0.0))
+        fallback = sorted(set(failed) | set(np.nonzero(bad.cpu().numpy())[0].tolist()))
         it_w = np.array([f["iters"] for f in rw.infos])   # (untimed, like the cold solves')
         for j, i in enumerate(failed):
             it_w[i] += rf.infos[j]["iters"]
