@@ -444,20 +444,19 @@ __global__ __launch_bounds__(64 * NW) void k_mlp_gemm(MlpLaunch p) {
 
 // Network input: Xb (rows x cols_p, BF16) <- (X - mean) * inv_std, zero padding,
 // and its transpose Xt (cols_p x rows_p) if given; clears `bad` (rows) if given.
-// A block takes 32 x 32 tiles in turn (one, up to HM_INPUT_BLOCKS of them: a second
-// grid dimension for the rows would end at 65,535 tiles, 2.1 million samples).
-#define HM_INPUT_BLOCKS 65536
+// A block takes 32 x 32 tiles of its 32 columns: one, up to the 65,535 blocks a second
+// grid dimension holds (2.1 million samples), then every 65,535th.
+#define HM_INPUT_ROWS 65535
 __global__ __launch_bounds__(256) void k_mlp_input(int rows, int rows_p, int cols, int cols_p, const float* __restrict__ X,
                                                    const float* __restrict__ mean, const float* __restrict__ inv_std,
                                                    uint16_t* __restrict__ Xb, uint16_t* __restrict__ Xt,
                                                    int* __restrict__ bad) {
   __shared__ uint16_t tile[32][33];
+  const int c0 = blockIdx.x * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
-  const unsigned tiles_c = (cols_p + 31) / 32, tiles = tiles_c * ((rows_p + 31) / 32);   // (4 KB of X each: below 2^31)
-  for (unsigned t = blockIdx.x; t < tiles; t += gridDim.x) {
-    const int c0 = (int)(t % tiles_c) * 32, r0 = (int)(t / tiles_c) * 32;
-    const int c = c0 + tx;
-    const float mu = c < cols ? mean[c] : 0.0f, is = c < cols ? inv_std[c] : 0.0f;
+  const int c = c0 + tx;
+  const float mu = c < cols ? mean[c] : 0.0f, is = c < cols ? inv_std[c] : 0.0f;
+  for (int r0 = blockIdx.y * 32;;) {
 #pragma unroll
     for (int y = ty; y < 32; y += 8) {
       const int r = r0 + y;
@@ -466,13 +465,16 @@ __global__ __launch_bounds__(256) void k_mlp_input(int rows, int rows_p, int col
       if (r < rows && c < cols_p) Xb[(long long)r * cols_p + c] = u;
       if (Xt) tile[y][tx] = u;
     }
-    if (bad && c0 == 0 && threadIdx.x < 32 && r0 + (int)threadIdx.x < rows) bad[r0 + threadIdx.x] = 0;
-    if (!Xt) continue;
-    __syncthreads();
+    if (bad && blockIdx.x == 0 && threadIdx.x < 32 && r0 + (int)threadIdx.x < rows) bad[r0 + threadIdx.x] = 0;
+    if (Xt) {
+      __syncthreads();
 #pragma unroll
-    for (int y = ty; y < 32; y += 8)
-      if (c0 + y < cols_p && r0 + tx < rows_p) Xt[(long long)(c0 + y) * rows_p + r0 + tx] = tile[tx][y];
-    if (t + gridDim.x < tiles) __syncthreads();   // (the next tile)
+      for (int y = ty; y < 32; y += 8)
+        if (c0 + y < cols_p && r0 + tx < rows_p) Xt[(long long)(c0 + y) * rows_p + r0 + tx] = tile[tx][y];
+    }
+    if (rows_p - r0 <= 32 * HM_INPUT_ROWS) return;
+    r0 += 32 * HM_INPUT_ROWS;
+    if (Xt) __syncthreads();   // (the next tile)
   }
 }
 
@@ -881,8 +883,7 @@ int forward_impl(hprqp_mlp& n, int B, const float* X, const MlpOut& out) {
   const int in = n.d[0], h1 = n.d[1], h2 = n.d[2], no = n.d[3];
   const int inp = n.dp[0], h1p = n.dp[1], h2p = n.dp[2], outp = n.dp[3];
   const int Bp = rup8(B);
-  const long long in_tiles = (long long)((inp + 31) / 32) * ((Bp + 31) / 32);
-  k_mlp_input<<<(int)std::min<long long>(in_tiles, HM_INPUT_BLOCKS), 256, 0, n.st>>>(
+  k_mlp_input<<<dim3((inp + 31) / 32, std::min((Bp + 31) / 32, HM_INPUT_ROWS)), 256, 0, n.st>>>(
       B, Bp, in, inp, X, n.in_mean, n.in_istd, n.Xb, train ? n.Xt : nullptr, out.bad);
   n.nev = 0;
   mark(n);
