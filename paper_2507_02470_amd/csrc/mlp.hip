@@ -232,6 +232,7 @@ __device__ __forceinline__ hm_f32x16 mlp_tile(const MlpJob& J, int i0, int j0, i
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
   auto mul = [&](int s, int k0) {
+    exchange();   // (here, and not behind the reads: the loads of a later slab may pass them)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       lds[(lr + 8 * q) * 8 + (lc ^ lr)] = a[s][q];
@@ -244,7 +245,6 @@ __device__ __forceinline__ hm_f32x16 mlp_tile(const MlpJob& J, int i0, int j0, i
       fa[u] = lds[li * 8 + ((2 * u + lh) ^ (li & 7))];
       fb[u] = lds[256 + li * 8 + ((2 * u + lh) ^ (li & 7))];
     }
-    exchange();
     const bool part = k0 + HM_SLAB > kend;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
