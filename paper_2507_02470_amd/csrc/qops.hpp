@@ -50,12 +50,13 @@ __host__ __device__ inline long long gemm_b_base(int transb, int ldb, int j0) {
 __host__ __device__ inline unsigned gemm_b_offset(int transb, unsigned ldb, unsigned j, unsigned k) {
   return 8u * (transb ? j + ldb * k : j * ldb + k);
 }
-// ONE: a block per tile (kgroups 1).  In a loop over tiles the compiler forms what does
-// not change in front of it, for all three terms, and a product of a block or two of K
-// a wave is bound by the instructions up to its first load (16 x 16 tiles, us of an
-// iteration at d = 8, 128, 160, 256: 8.0, 11.5, 13.1, 15.8 in the loop, 6.7, 10.3, 11.1, 13.4
-// so; the larger tiles have more K a wave).
-template <class Epi, bool PART, int WM, int WN, int NW, bool SHORT = false, bool ONE = false>
+// ONE: a block per tile (kgroups 1), of one term (1) or up to three (3).  In a loop over
+// tiles the compiler forms what does not change in front of it, for all three terms, and
+// a product of a block or two of K a wave is bound by the instructions up to its first
+// load (16 x 16 tiles, us of an iteration of one term at d = 8, 128, 160, 256: 8.0, 11.5, 13.1,
+// 15.8 in the loop, 6.9, 10.3, 11.1, 13.3 without it, 6.5, 9.8, 10.7, 13.1 for one term; the
+// larger tiles have more K a wave).
+template <class Epi, bool PART, int WM, int WN, int NW, bool SHORT = false, int ONE = 0>
 __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int ldo, Epi epi,
                                                    const DevParams* __restrict__ prm, int jit, RedOut red, int kgroups,
                                                    double* __restrict__ parts) {
@@ -70,11 +71,12 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
   const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
   const int tiles = tiles_m * tiles_n;
   const int n0 = (op.K[0] + 15) / 16;
-  const int n1 = op.nt > 1 ? (op.K[1] + 15) / 16 : 0;
-  const int n2 = op.nt > 2 ? (op.K[2] + 15) / 16 : 0;
+  constexpr bool TERMS = ONE != 1;   // up to three terms, else one
+  const int n1 = TERMS && op.nt > 1 ? (op.K[1] + 15) / 16 : 0;
+  const int n2 = TERMS && op.nt > 2 ? (op.K[2] + 15) / 16 : 0;
   const int total = n0 + n1 + n2;
   const int per = (total + kgroups - 1) / kgroups;
-  auto pick = [&](int t, auto x0, auto x1, auto x2) { return t == 0 ? x0 : t == 1 ? x1 : x2; };
+  auto pick = [&](int t, auto x0, auto x1, auto x2) { return !TERMS || t == 0 ? x0 : t == 1 ? x1 : x2; };
   Epi e = epi;
   if (!ONE) e.setup(prm, jit);
   double acc[NR > 0 ? NR : 1];
@@ -141,7 +143,7 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
       }
       // the next block; after the last one that is loaded again, unread
       if (lc.cc + 1 < lc.nc) ++lc.cc;
-      else if (lc.t + 1 < op.nt) load_term(lc.t + 1, 0);
+      else if (TERMS && lc.t + 1 < op.nt) load_term(lc.t + 1, 0);
     };
     hq_dx4 d[WM][WN];
 #pragma unroll
@@ -174,10 +176,10 @@ __global__ __launch_bounds__(64 * NW) void k_dgemm(int M, int N, GemmOps op, int
             d[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.b[s][n], f.a[s][m], d[m][n], 0, 0, 0);
       }
       if (mc + 1 < pick(mt, n0, n1, n2)) ++mc;
-      else if (mt + 1 < op.nt) { ++mt; mc = 0; }
+      else if (TERMS && mt + 1 < op.nt) { ++mt; mc = 0; }
     };
     auto start = [&] {
-      const int t0 = c0 >= n0 + n1 ? 2 : c0 >= n0 ? 1 : 0;
+      const int t0 = !TERMS ? 0 : c0 >= n0 + n1 ? 2 : c0 >= n0 ? 1 : 0;
       mt = t0;
       mc = c0 - pick(t0, 0, n0, n0 + n1);
       load_term(mt, mc);

@@ -586,8 +586,8 @@ void launch_gemm_tile(hprqp_handle& h, int M, int N, const GemmOps& ops, const E
     check_red_grid(grid, red);
     if constexpr (WM * WN == 1) {
       if (tiles == grid) {
-        k_dgemm<Epi, false, WM, WN, NW, SHORT, true><<<grid, 64 * NW, 0, h.st>>>(M, N, ops, M, epi, h.dprm, j, red, 1,
-                                                                               nullptr);
+        const auto k = ops.nt == 1 ? k_dgemm<Epi, false, WM, WN, NW, SHORT, 1> : k_dgemm<Epi, false, WM, WN, NW, SHORT, 3>;
+        k<<<grid, 64 * NW, 0, h.st>>>(M, N, ops, M, epi, h.dprm, j, red, 1, nullptr);
         return;
       }
     }
